@@ -173,7 +173,7 @@ struct foap4_mesh {
   bool pat_valid = false;
   double *d_scal = nullptr;
   bool dt_valid = false;
-  f4::MeshDev *d_dev = nullptr;  // single-mesh descriptor for the plain path
+  f4::MeshDev *d_dev = nullptr;  // two descriptors of this mesh: stored ghosts, and the steps' (gathered halos)
   int64_t *d_item_begin = nullptr;
   // refinement indicator: default for regrid, attached MLP, scratch
   foap4_indicator ind = FOAP4_IND_LOHNER;
