@@ -1,7 +1,7 @@
 """Builds libfoap4.so (HIP for gfx950) in-tree with hipcc.
 
-Every source is compiled to an object under _build/ (stage.hip once per
-scheme) and the objects are linked into paper_2605_07612_amd/libfoap4.so.  Packed FP32 instructions are
+Every source is compiled to an object under _build/ (stage.hip and weno.hip
+once per scheme) and the objects are linked into paper_2605_07612_amd/libfoap4.so.  Packed FP32 instructions are
 disabled for all device code.
 """
 from __future__ import annotations
@@ -19,11 +19,13 @@ BUILD = os.path.join(ROOT, "_build", "foap4")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["topology.cpp", "capi.cpp", "pattern.hip", "ghost.hip", "reduce.hip", "regrid.hip", "mlp.hip", "weno.hip", "advect.hip"]
+SOURCES = ["topology.cpp", "capi.cpp", "pattern.hip", "ghost.hip", "reduce.hip", "regrid.hip", "mlp.hip", "advect.hip"]
 # the stage kernels, one compile per scheme bit mask (limiter, flux, gravity)
 N_SCHEMES = 8
 UNITS = [(s, [], s) for s in SOURCES] + [("stage.hip", [f"-DF4_SCHEME={k}"], f"stage_s{k}.hip")
                                          for k in range(N_SCHEMES)]
+# the WENO5 kernels, one compile per HLL and gravity bits (no limiter bit)
+UNITS += [("weno.hip", [f"-DF4_SCHEME={k}"], f"weno_s{k}.hip") for k in (0, 2, 4, 6)]
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=on", f"--offload-arch={ARCH}", "-I" + os.path.join(ROOT, "include"),
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]

@@ -29,10 +29,6 @@ foap4_status fail(foap4_mesh *m, foap4_status s, const std::string &msg) {
 // records measure faster.
 static bool srl_x_by_block(const foap4_mesh *m) { return m->d.ndim == 3 && m->d.block_n >= 16; }
 
-// Whether the stages of a step read same-level halos straight from the
-// neighbouring blocks: all but the WENO5 kernels do.
-static bool step_gathers(const foap4_mesh *m) { return m->d.limiter != FOAP4_LIM_WENO5 || m->nvar == 1; }
-
 MeshDev make_dev(const foap4_mesh *m, int ks, int gather, bool x_by_block) {
   MeshDev d{};
   d.s[0] = m->state[0];
@@ -93,7 +89,7 @@ MeshDev make_dev(const foap4_mesh *m, int ks, int gather, bool x_by_block) {
 // the stored ghosts (fill, flags, features, remap), m->d_dev[1] for the
 // steps, whose stage kernels read same-level halos from the neighbours.
 foap4_status upload_dev(foap4_mesh *m) {
-  const MeshDev d[2] = {make_dev(m, 1, 0, true), make_dev(m, 1, step_gathers(m))};
+  const MeshDev d[2] = {make_dev(m, 1, 0, true), make_dev(m, 1, 1)};
   F4_HIP(m, hipMemcpyAsync(m->d_dev, d, sizeof(d), hipMemcpyHostToDevice, m->stream));
   F4_HIP(m, hipStreamSynchronize(m->stream));
   return FOAP4_OK;
@@ -141,7 +137,7 @@ static foap4_status fill(foap4_mesh *m, const MeshDev *dd, int which) {
   return FOAP4_OK;
 }
 
-// Ghost cells that one stage of a step reads.  Gathering stages take their
+// Ghost cells that one stage of a step reads.  The stages take their
 // same-level halos from the neighbours' interiors, so R1 runs only the
 // restrictions, the boundary faces and the SRL records whose ghosts a
 // prolongation stencil reaches, and a uniform periodic mesh runs nothing.
@@ -149,7 +145,6 @@ static foap4_status fill(foap4_mesh *m, const MeshDev *dd, int which) {
 // extra pass over the halos: 346 of the 924 us of an FP64 stage on 256^3 cells
 // in 16^3 blocks.
 static foap4_status fill_step(foap4_mesh *m, int which) {
-  if (!step_gathers(m)) return fill(m, m->d_dev, which);
   const bool f64 = m->d.prec == FOAP4_F64;
   const int64_t r1 = (int64_t)m->pat.n_srl_c2f + m->pat.n[kF2C] + m->pat.n[kBC], r2 = m->pat.n[kC2F];
   F4_HIP(m, launch_ghost(m->d_dev + 1, 1, r1, 1, which, m->d.ndim, f64, 0, m->stream, m->nvar));
@@ -182,8 +177,8 @@ struct foap4_batch {
   int nmask = 0;
   int scheme = 0;  // scheme_of() shared by all meshes
   int integrator = 0;  // shared time integrator
-  bool weno = false;   // WENO5 meshes: their own stage kernel per mesh, stored ghosts
-  bool adv = false;    // scalar advection meshes: the advection kernel per mesh, stored ghosts
+  bool weno = false;   // WENO5 meshes: their own stage kernel per mesh
+  bool adv = false;    // scalar advection meshes: the advection kernel per mesh
   hipStream_t stream = nullptr, cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -758,7 +753,7 @@ static foap4_status batch_upload(foap4_batch *b) {
   std::vector<MeshDev> devs;
   int64_t it = 0, r1 = 0, r2 = 0;
   for (foap4_mesh *m : b->meshes) {
-    MeshDev d = make_dev(m, b->ks, b->weno ? 0 : b->gather);
+    MeshDev d = make_dev(m, b->ks, b->gather);
     d.item_begin = it;
     d.r1_begin = r1;
     d.r2_begin = r2;

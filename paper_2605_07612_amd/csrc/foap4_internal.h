@@ -255,7 +255,7 @@ int64_t stage_items_for(int ndim, int N, int64_t nb, int ks);
 hipError_t launch_stage(const MeshDev *d_meshes, int n_meshes, int64_t total_items, int stage,
                         int ndim, bool f64, int grid, hipStream_t s, int xcd, int nmask, int scheme,
                         const SubStep &ss = SubStep{});
-// weno.hip: the WENO5 stage (one thread per interior cell, stored ghosts)
+// weno.hip: the WENO5 stage (one workgroup per tile and k-slab)
 hipError_t launch_weno_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int stage, int ndim, bool f64,
                              int scheme, hipStream_t s, const SubStep &ss = SubStep{});
 // advect.hip: the scalar advection stage (one workgroup per block, stored ghosts)

@@ -103,6 +103,36 @@ def test_parity(f4, name, integ, flux, prec):
     assert abs(t - om.t) <= (1e-13 if prec == 1 else 1e-5) * om.t
 
 
+@pytest.mark.parametrize("prec", [1, 0], ids=["f64", "f32"])
+@pytest.mark.parametrize("ndim,N,g,trees", [(3, 8, 4, (1, 1, 1)), (3, 8, 3, (10, 9, 12)), (3, 16, 3, (3, 2, 1)),
+                                            (3, 16, 4, (9, 8, 11)), (3, 32, 3, (1, 1, 1)), (3, 32, 3, (2, 3, 2)),
+                                            (2, 8, 3, (3, 1, 1)), (2, 16, 4, (1, 2, 1)), (2, 32, 3, (3, 2, 1))])
+def test_tiles_and_slabs(f4, ndim, N, g, trees, prec):
+    """One Heun step with walls along the last axis on meshes on both sides of
+    the slab rule (slabs of 1 plane up to whole tiles; 8^3 blocks: 1 and 1080,
+    16^3: 6 and 792, 32^3: 1 and 12), in every tile shape and with blocks that
+    are their own neighbours."""
+    size = 1.0 / max(trees)
+
+    def field(*x):
+        s = sum(np.sin(2 * np.pi * (d + 1) * x[d] / (trees[d] * size) + d) for d in range(ndim))
+        rho = 1.0 + 0.1 * s
+        return synth.conserved_from_primitive(rho, [0.1 * s] * ndim, 1.0 + 0.05 * s, 1.4)
+
+    bt, bv = f4.wall_bc(ndim)
+    w = dict(name=f"tiles{ndim}d_b{N}_{trees}", ndim=ndim, trees=trees, N=N, g=g, tree_size=size, gamma=1.4, cfl=0.5,
+             field=field, limiter="weno5", flux="rusanov", integrator="heun", gravity=(0.0, 0.3, 0.2)[:ndim],
+             periodic=tuple(d != ndim - 1 for d in range(3)), bc_type=bt, bc_value=bv)
+    gm, om = build(w, prec)
+    gm.step(1)
+    om.step(1)
+    a = interior(gpu_state(gm), g, N, ndim)
+    err, _ = check_state(a, om.interior(), gm.export()[0], ndim, size, N, prec)
+    say(w["name"], "prec", prec, "rel L1", err)
+    assert err <= TOL[prec]
+    assert abs(gm.time()[0] - om.t) <= (1e-13 if prec == 1 else 1e-5) * om.t
+
+
 def test_conservation_on_two_levels(f4):
     w = case("blast3d", "heun")
     gm, _ = build(w, 1)
