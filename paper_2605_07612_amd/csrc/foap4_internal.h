@@ -195,16 +195,26 @@ struct foap4_mesh {
   std::string err;
 };
 
+namespace f4 {
+// what one loss and gradient evaluation returns
+struct MlpResult {
+  double loss;
+  unsigned long long cnt[4];  // label counts (classes, invalid)
+  float grad[kMlpParams];
+};
+}  // namespace f4
+
 // Learned refinement indicator: FP32 master weights, FP64 Adam moments,
 // BF16 MFMA operand fragments and the gradient workspace, all on the device.
 struct foap4_mlp {
   hipStream_t stream = nullptr;
   float *d_w = nullptr;        // [kMlpParams] flat W1 b1 W2 b2 W3 b3
   double *d_mv = nullptr;      // [2][kMlpParams] Adam first and second moments
-  float *d_grad = nullptr;     // [kMlpParams] last gradient
+  f4::MlpResult *d_res = nullptr, *h_res = nullptr;  // last evaluation, on the device and in pinned host memory
   void *d_frag = nullptr;      // [kMlpFrags][64] 16-byte operand fragments
   float *d_cls = nullptr;      // [4] per-class sample weight of the loss
-  unsigned long long *d_cnt = nullptr;  // [4] label counts (classes, invalid)
+  unsigned long long *d_cnt = nullptr;  // label counts per counting workgroup (classes, invalid)
+  unsigned *d_ticket = nullptr;         // counting workgroups done (0 between launches)
   float *d_part = nullptr;     // [groups][kMlpPartStride] per-workgroup partial gradients
   size_t cap_part = 0;         // in workgroups
   double *d_loss = nullptr;    // [cap_loss] loss per iteration

@@ -162,6 +162,29 @@ def test_gradient_matches_oracle(f4, n):
         o += k
 
 
+@pytest.mark.parametrize("n", [1, 128, 129, 2048, 2049, 65536, 66001])
+def test_counts_and_reduction_edges(f4, n):
+    """Loss and gradient at the edges of the reduction's runs (1, 2, 16, 17 and
+    512 workgroups of partials) and of the label count (fewer rows than
+    counting threads, and more than one round of them), and a single bad label
+    first, last and at -2."""
+    X, y = rows(n, 91)
+    w = omlp.init_weights(7).astype(np.float32)
+    cw = np.array([1.0, 4.0, 0.25])
+    net = f4.Mlp(w)
+    lo, go = omlp.loss_and_grad(w.astype(np.float64), X.astype(np.float64), y, cw, emulate=True)
+    for _ in range(2):  # the count's ticket is back at zero after a call
+        loss, g = net.loss_grad(to_dev(X), to_dev(y), cw)
+        assert loss == pytest.approx(lo, rel=1e-5)
+        assert np.linalg.norm(g - go) <= 1e-3 * np.linalg.norm(go)
+    for at, bad in ((0, 2), (n - 1, 127), (n // 2, -2)):
+        z = y.copy()
+        z[at] = bad
+        with pytest.raises(f4.Foap4Error, match="E_INVALID"):
+            net.loss_grad(to_dev(X), to_dev(z), cw)
+    assert net.loss_grad(to_dev(X), to_dev(y), cw)[0] == loss
+
+
 def test_gradient_deterministic(f4):
     X, y = rows(20000, 41)
     net = f4.Mlp(omlp.init_weights(2).astype(np.float32))
