@@ -7,26 +7,27 @@
 
 namespace f4 {
 
-// CFL inverse time step sum_d (|v_d| + c) / dx of one cell.  FP64 states use
-// the operation order of the definition without contraction (equal to a plain
-// evaluation); FP32 states evaluate it in FP32 with the hardware reciprocal
-// and square root, and the maximum over cells is reduced in FP64 (an FP32
-// maximum converts exactly, so a kernel may keep its running maximum in FP32).
+// CFL inverse time step sum_d (|v_d| + c) / dx of one cell, with one
+// reciprocal of the density and the inverse cell width: FP64 states with the
+// refined reciprocal and square root (a few ulp; the IEEE divisions and root
+// of the plain evaluation cost 136 instructions a cell, a fifth of the stage),
+// FP32 states in FP32 with the hardware ones.  The maximum over cells is
+// reduced in FP64 (an FP32 maximum converts exactly, so a kernel may keep its
+// running maximum in FP32).
 template <int NDIM>
-__device__ __forceinline__ double cell_inv_dt(const double *U, double gamma, double dx, bool &bad) {
-#pragma clang fp contract(off)
+__device__ __forceinline__ double cell_inv_dt(const double *U, double gamma, double idx, bool &bad) {
   const double r = U[0];
-  double ke = 0.0, v[3];
+  const double ir = rcp_nr(r);
+  double ke = 0.0, sv = 0.0;
 #pragma unroll
   for (int d = 0; d < NDIM; d++) {
-    v[d] = U[1 + d] / r;
-    ke += U[1 + d] * v[d];
+    const double v = U[1 + d] * ir;
+    ke += U[1 + d] * v;
+    sv += fabs(v);
   }
   const double p = (gamma - 1.0) * (U[NDIM + 1] - 0.5 * ke);
-  const double cs = sqrt(gamma * p / r);
-  double s = 0.0;
-#pragma unroll
-  for (int d = 0; d < NDIM; d++) s += (fabs(v[d]) + cs) / dx;
+  const double cs = sqrt_nr(gamma * p * ir);
+  const double s = (sv + NDIM * cs) * idx;
   bad |= !(r > 0.0) || !(p > 0.0) || !isfinite(s);
   return s;
 }
