@@ -380,7 +380,8 @@ foap4_status foap4_batch_create(foap4_mesh *const *meshes, int32_t n_meshes, foa
 foap4_status foap4_batch_destroy(foap4_batch *batch);
 
 /* Work decomposition of the batched stage kernel: kslabs = 1, 2 or 4 k-slabs
- * per block tile (the LDS tile depth is N / kslabs planes), wg_stage1 and
+ * per block tile at least (a batch that would leave compute units idle takes
+ * thinner slabs; the results are identical), wg_stage1 and
  * wg_stage2 = workgroups per compute unit of the persistent grid of the
  * first and the second Heun stage (0: one workgroup per work item, no
  * persistence; the two stages differ in registers and traffic, so their

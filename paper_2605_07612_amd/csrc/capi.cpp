@@ -29,6 +29,51 @@ foap4_status fail(foap4_mesh *m, foap4_status s, const std::string &msg) {
 // records measure faster.
 static bool srl_x_by_block(const foap4_mesh *m) { return m->d.ndim == 3 && m->d.block_n >= 16; }
 
+// Planes per work item of a MUSCL stage launch over the given meshes (3D): a
+// tile is split along z into slabs of a power of two of planes where whole
+// tiles leave CUs idle or end in a nearly empty round.  A launch of I items
+// puts n = ceil(I / CUs) on a CU; S of them run at once (by registers and
+// LDS), and a round of r <= S items takes about (r + 1.25 S) / (2.25 S) of a
+// full one, because few waves wait more on their own chains.  An item costs
+// its planes plus two (the planes around a slab are loaded and converted
+// again).  The least of rounds x planes is taken.  Measured, two Heun steps in
+// us by planes per item (the choice marked): FP32 180 blocks of 16^3: 163 (16),
+// 126 (8), 102 (4)*, 105 (2); 512 blocks: 190 (16), 152 (8)*, 173 (4); 720: 211
+// (16)*, 219 (8); 80 blocks of 32^3: 327 (32), 219 (16)*, 218 (8), 235 (4); one:
+// 275 (32), 52 (1)*; FP64 180 of 16^3: 204 (16), 162 (8)*, 176 (4); 27 of 32^3:
+// 204 (16), 156 (8)*, 196 (4); 512 of 8^3: FP32 96 (8), 82 (4), 85 (2)*.
+static int slab_planes(foap4_mesh *const *meshes, size_t n_meshes, int n_cu) {
+  int largest = 0, smallest = 64;
+  for (size_t i = 0; i < n_meshes; i++) {
+    largest = std::max(largest, (int)meshes[i]->d.block_n);
+    smallest = std::min(smallest, (int)meshes[i]->d.block_n);
+  }
+  const bool f64 = meshes[0]->d.prec == FOAP4_F64, mixed = smallest != largest;
+  const int at_once = f64 ? (smallest == 8 || mixed ? 1 : 2) : (smallest == 8 || mixed ? 3 : 4);
+  int best = largest;
+  double best_cost = 0.0;
+  for (int kd = largest; kd >= 1; kd /= 2) {
+    int64_t items = 0;
+    for (size_t i = 0; i < n_meshes; i++) {
+      const int N = meshes[i]->d.block_n;
+      items += stage_items_for(3, N, (int64_t)meshes[i]->topo.leaves.size(), std::max(1, N / kd));
+    }
+    const int64_t n = (items + n_cu - 1) / n_cu, full = n / at_once, rest = n % at_once;
+    const double rounds = (double)full + (rest ? (rest + 1.25 * at_once) / (2.25 * at_once) : 0.0);
+    const double cost = rounds * (kd + 2);
+    if (kd == largest || cost < best_cost) {
+      best = kd;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// k-slabs per tile of a mesh's own steps
+static int step_slabs(foap4_mesh *m) {
+  return m->d.ndim == 3 ? m->d.block_n / slab_planes(&m, 1, m->n_cu) : 1;
+}
+
 MeshDev make_dev(const foap4_mesh *m, int ks, int gather, bool x_by_block) {
   MeshDev d{};
   d.s[0] = m->state[0];
@@ -70,7 +115,7 @@ MeshDev make_dev(const foap4_mesh *m, int ks, int gather, bool x_by_block) {
   d.cur = m->cur;
   d.N = m->d.block_n;
   d.g = m->d.n_ghost;
-  d.ks = std::max(1, std::min(ks, m->d.block_n / 8));
+  d.ks = std::max(1, ks);
   d.gather = gather;
   // with gathered halos the SRL ghosts are needed only as input of the C2F
   // prolongation stencils: the SRL records with a side that is the coarse
@@ -89,7 +134,7 @@ MeshDev make_dev(const foap4_mesh *m, int ks, int gather, bool x_by_block) {
 // the stored ghosts (fill, flags, features, remap), m->d_dev[1] for the
 // steps, whose stage kernels read same-level halos from the neighbours.
 foap4_status upload_dev(foap4_mesh *m) {
-  const MeshDev d[2] = {make_dev(m, 1, 0, true), make_dev(m, 1, 1)};
+  const MeshDev d[2] = {make_dev(m, 1, 0, true), make_dev(m, step_slabs(m), 1)};
   F4_HIP(m, hipMemcpyAsync(m->d_dev, d, sizeof(d), hipMemcpyHostToDevice, m->stream));
   F4_HIP(m, hipStreamSynchronize(m->stream));
   return FOAP4_OK;
@@ -283,8 +328,9 @@ foap4_status foap4_mesh_create(const foap4_mesh_desc *desc, void *state0, void *
   }
   m->cap_blocks = cap;
   // set-up of the allocation-free totals on this device (once per device)
-  if (hipGetDevice(&m->device) != hipSuccess || noalloc_scratch_init(m->device) != hipSuccess) {
-    m->err = "device scratch lookup failed";
+  if (hipGetDevice(&m->device) != hipSuccess || noalloc_scratch_init(m->device) != hipSuccess ||
+      hipDeviceGetAttribute(&m->n_cu, hipDeviceAttributeMultiprocessorCount, m->device) != hipSuccess || m->n_cu < 1) {
+    m->err = "device scratch or attribute lookup failed";
     return bail(FOAP4_E_HIP);
   }
   if (hipMemsetAsync(m->d_scal, 0, kNScal * 8, m->stream) != hipSuccess) {
@@ -448,7 +494,7 @@ foap4_status foap4_step(foap4_mesh *m, int32_t n_steps, double *t_out, double *d
   if (nsub) {
     const bool f64 = m->d.prec == FOAP4_F64;
     const int ndim = m->d.ndim;
-    const int64_t items = stage_items_for(ndim, m->d.block_n, (int64_t)m->topo.leaves.size(), 1);
+    const int64_t items = stage_items_for(ndim, m->d.block_n, (int64_t)m->topo.leaves.size(), step_slabs(m));
     foap4_status st;
     if ((st = ensure_dt(m)) != FOAP4_OK) return st;
     for (int32_t s = 0; s < n_steps; s++) {
@@ -466,7 +512,7 @@ foap4_status foap4_step(foap4_mesh *m, int32_t n_steps, double *t_out, double *d
   }
   const bool f64 = m->d.prec == FOAP4_F64;
   const int ndim = m->d.ndim;
-  const int64_t items = stage_items_for(ndim, m->d.block_n, (int64_t)m->topo.leaves.size(), 1);
+  const int64_t items = stage_items_for(ndim, m->d.block_n, (int64_t)m->topo.leaves.size(), step_slabs(m));
   foap4_status st;
   if ((st = ensure_dt(m)) != FOAP4_OK) return st;
   const size_t nb = m->topo.leaves.size();
@@ -752,8 +798,11 @@ static void drop_graph(foap4_batch *b) {
 static foap4_status batch_upload(foap4_batch *b) {
   std::vector<MeshDev> devs;
   int64_t it = 0, r1 = 0, r2 = 0;
+  // slabs as configured, or thinner ones where the batch would not fill the chip
+  const int kd = b->ndim == 3 ? slab_planes(b->meshes.data(), b->meshes.size(), b->n_cu) : 1;
   for (foap4_mesh *m : b->meshes) {
-    MeshDev d = make_dev(m, b->ks, b->gather);
+    const int N = m->d.block_n;
+    MeshDev d = make_dev(m, b->ndim == 3 ? std::max(std::min(b->ks, N / 8), N / kd) : 1, b->gather);
     d.item_begin = it;
     d.r1_begin = r1;
     d.r2_begin = r2;

@@ -162,6 +162,7 @@ struct foap4_mesh {
   size_t state_bytes = 0;
   hipStream_t stream = nullptr;
   int device = 0;              // HIP device current at creation
+  int n_cu = 256;              // its compute units
   int32_t cur = 0;
   f4::Topology topo;
   int64_t revision = 0;

@@ -311,6 +311,36 @@ def test_batch_two_level_equals_plain(f4, prec, gather, ndim, block):
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("N,trees", [(8, (1, 1, 1)), (8, (8, 8, 8)), (8, (11, 10, 10)), (16, (1, 2, 1)),
+                                     (16, (4, 4, 4)), (16, (6, 6, 5)), (16, (6, 6, 10)), (32, (1, 1, 1)),
+                                     (32, (3, 3, 3))])
+def test_slab_depths(f4, N, trees, prec):
+    """Two steps on meshes whose tiles are split into slabs of 1 up to N planes
+    (the fewer blocks, the thinner), in the plain form with the features of the
+    second step captured, and batched with a second mesh of another size, which
+    takes other slabs: equal to each other and to the oracle."""
+    w = small_uniform(N, trees)
+    gp, om = build_pair(w, prec)
+    gb, _ = build_pair(w, prec)
+    other, _ = build_pair(small_uniform(24 - N if N < 32 else 16, (2, 2, 3), seed=3), prec)
+    gp.step(1)
+    raw = gp.block_features(raw=True)[1].cpu().numpy()
+    gp.capture_features()
+    gp.step(1)
+    b = f4.Batch([gb, other])
+    b.step(2)
+    assert gp.time() == gb.time()
+    a, c = interior(gpu_state(gp), 2, N, 3), interior(gpu_state(gb), 2, N, 3)
+    assert np.array_equal(a, c)
+    cap = gp.captured_features(raw=True)[1].cpu().numpy()
+    assert np.max(np.abs(cap - raw)) <= (1e-12 if prec else 1e-5) * np.max(raw)
+    om.step(2)
+    err, _ = check_state(a, om.interior(), gp.export()[0], 3, w["tree_size"], N, prec)
+    say(w["name"], "prec", prec, "rel L1", err)
+    assert err <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 def test_batch_follows_regrid(f4, prec):
     """A batch keeps working across a regrid of its mesh (new leaf table,
     pattern and work items; the step graph is captured again): step, regrid
