@@ -177,8 +177,10 @@ static foap4_status fill(foap4_mesh *m, const MeshDev *dd, int which) {
   const int64_t r1 = m->pat.n[kSRL] - nx + m->pat.n[kF2C] + m->pat.n[kBC], r2 = m->pat.n[kC2F];
   if (nx) F4_HIP(m, launch_srl_x_blocks(dd, (int64_t)m->topo.leaves.size(), which, m->d.ndim, f64, m->stream,
                                         m->nvar));
-  F4_HIP(m, launch_ghost(dd, 1, r1, 1, which, m->d.ndim, f64, 0, m->stream, m->nvar));
-  if (r2) F4_HIP(m, launch_ghost(dd, 1, r2, 2, which, m->d.ndim, f64, 0, m->stream, m->nvar));
+  F4_HIP(m, launch_ghost(dd, 1, r1, 1, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->stream,
+                         m->nvar));
+  if (r2) F4_HIP(m, launch_ghost(dd, 1, r2, 2, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->stream,
+                         m->nvar));
   return FOAP4_OK;
 }
 
@@ -192,8 +194,10 @@ static foap4_status fill(foap4_mesh *m, const MeshDev *dd, int which) {
 static foap4_status fill_step(foap4_mesh *m, int which) {
   const bool f64 = m->d.prec == FOAP4_F64;
   const int64_t r1 = (int64_t)m->pat.n_srl_c2f + m->pat.n[kF2C] + m->pat.n[kBC], r2 = m->pat.n[kC2F];
-  F4_HIP(m, launch_ghost(m->d_dev + 1, 1, r1, 1, which, m->d.ndim, f64, 0, m->stream, m->nvar));
-  F4_HIP(m, launch_ghost(m->d_dev + 1, 1, r2, 2, which, m->d.ndim, f64, 0, m->stream, m->nvar));
+  F4_HIP(m, launch_ghost(m->d_dev + 1, 1, r1, 1, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->stream,
+                         m->nvar));
+  F4_HIP(m, launch_ghost(m->d_dev + 1, 1, r2, 2, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->stream,
+                         m->nvar));
   return FOAP4_OK;
 }
 
@@ -215,6 +219,7 @@ struct foap4_batch {
   std::vector<int64_t> revs, serials;
   int ndim = 3;
   int nv = 5;          // variables per cell, shared by all meshes
+  int max_n = 0, max_g = 0;  // largest block size and ghost width
   bool f64 = false;
   int ks = 1, wg1 = 0, wg2 = 0, gather = 1, xcd = 1;  // wg1 / wg2: workgroups per CU of stage 1 / 2
   MeshDev *d_devs = nullptr;
@@ -860,8 +865,8 @@ static hipError_t batch_enqueue_step(foap4_batch *b, hipStream_t s) {
   const int nsub = substeps_of(b->integrator, &subs);
   for (int k = 0; k < nsub; k++) {  // integrators with extra states: generic sub-steps
     const int which = subs[k].deriv;
-    if ((e = launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, 0, s, b->nv)) != hipSuccess) return e;
-    if (b->r2_total && (e = launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, 0, s, b->nv)) != hipSuccess)
+    if ((e = launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv)) != hipSuccess) return e;
+    if (b->r2_total && (e = launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv)) != hipSuccess)
       return e;
     const int form = substep_form(subs[k]);
     if ((e = batch_stage(b, form, stage_grid(b, 2), s, subs[k])) != hipSuccess) return e;
@@ -874,8 +879,8 @@ static hipError_t batch_enqueue_step(foap4_batch *b, hipStream_t s) {
   for (int stage = 1; stage <= 2; stage++) {
     const int which = stage - 1;
     const int grid = stage_grid(b, stage);
-    if ((e = launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, 0, s, b->nv)) != hipSuccess) return e;
-    if (b->r2_total && (e = launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, 0, s, b->nv)) != hipSuccess)
+    if ((e = launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv)) != hipSuccess) return e;
+    if (b->r2_total && (e = launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv)) != hipSuccess)
       return e;
     if ((e = batch_stage(b, stage, grid, s)) != hipSuccess) return e;
     for (int i = 0; i < n; i++)
@@ -928,6 +933,8 @@ foap4_status foap4_batch_create(foap4_mesh *const *meshes, int32_t n, foap4_batc
       return fail(nullptr, FOAP4_E_INVALID, "null mesh in batch");
     }
     b->meshes.push_back(meshes[i]);
+    b->max_n = std::max(b->max_n, (int)meshes[i]->d.block_n);
+    b->max_g = std::max(b->max_g, (int)meshes[i]->d.n_ghost);
     b->revs.push_back(-1);
     b->serials.push_back(-1);
   }
@@ -1027,9 +1034,9 @@ foap4_status foap4_batch_phase_times(foap4_batch *b, int32_t n_steps, double *ou
   for (int it = 0; it < n_steps; it++) {
     for (int stage = 1; stage <= 2; stage++) {
       const int which = stage - 1;
-      B_HIP(b, launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, 0, s, b->nv));
+      B_HIP(b, launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv));
       B_HIP(b, hipEventRecord(ev[++k], s));
-      if (b->r2_total) B_HIP(b, launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, 0, s, b->nv));
+      if (b->r2_total) B_HIP(b, launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv));
       B_HIP(b, hipEventRecord(ev[++k], s));
       B_HIP(b, batch_stage(b, stage, stage_grid(b, stage), s));
       B_HIP(b, hipEventRecord(ev[++k], s));

@@ -127,9 +127,9 @@ struct MeshDev {
   int32_t gather;             // stage reads same-level halos from the neighbours
   int32_t r1_srl;             // SRL records executed in round R1: all pn[kSRL] with stored
                               // ghosts, with gathered halos only those C2F prolongation
-                              // reads (indices in srl_sub); R1 then runs pn[kF2C]
+                              // reads (in srl_sub); R1 then runs pn[kF2C]
                               // restrictions and pn[kBC] boundary faces
-  const int32_t *srl_sub;     // with gathered halos: the SRL records R1 runs, else null
+  const int32_t *srl_sub;     // with gathered halos: the SRL records R1 runs as (a, b, face), else null
   int32_t srl_first;          // without srl_sub: the first SRL record R1 runs (the
                               // records before it, the x faces, are copied by block in
                               // launch_srl_x_blocks)
@@ -146,7 +146,7 @@ struct Pattern {
   void *bflux_f = nullptr, *bflux_c = nullptr;
   size_t cap[8] = {};           // capacities in bytes of the buffers above
   size_t cap_bflux[2] = {};
-  int32_t *srl_c2f = nullptr;   // SRL record indices whose ghosts C2F prolongation reads
+  int32_t *srl_c2f = nullptr;   // SRL records whose ghosts C2F prolongation reads: (a, b, face)
   int32_t n_srl_c2f = 0;
   size_t cap_srl_c2f = 0;
 };
@@ -249,9 +249,10 @@ foap4_status upload_dev(foap4_mesh *m);
 foap4_status build_pattern(foap4_mesh *m);
 // ghost.hip: round 1 = SRL + F2C + boundary, round 2 = C2F; which = state role
 // (0 current, 1 other, 2 third)
-// nv: variables per cell (ndim + 2 for the Euler system, 1 for scalar advection)
+// nv: variables per cell (ndim + 2 for the Euler system, 1 for scalar advection);
+// block_n, n_ghost: the largest of the meshes'
 hipError_t launch_ghost(const MeshDev *d_meshes, int n_meshes, int64_t total, int round, int which,
-                        int ndim, bool f64, int grid, hipStream_t s, int nv);
+                        int ndim, bool f64, int block_n, int n_ghost, hipStream_t s, int nv);
 // Same-level x faces of a single 3D mesh with stored ghosts, by block: block
 // b's first g columns into its -x neighbour's +x ghosts, its last g columns
 // into its +x neighbour's -x ghosts (the x-face SRL records, done by block).

@@ -1,4 +1,5 @@
-// Execution of the stored ghost pattern (Sec. 2.6), one workgroup per record.
+// Execution of the stored ghost pattern (Sec. 2.6), one or more workgroups per
+// record.
 //   round R1: SRL records (copy g layers both ways across a face pair),
 //             F2C records (coarse ghost = mean of the 2^d fine cells, FP64)
 //             and physical boundary faces (Sec. 2.4: Dirichlet / Neumann
@@ -8,6 +9,8 @@
 // Work items of several meshes are concatenated (r1_begin / r2_begin).
 // NV, the number of variables per cell, is a template parameter: ndim + 2
 // for the Euler system, 1 for scalar advection.
+#include <algorithm>
+
 #include "foap4_internal.h"
 
 namespace f4 {
@@ -30,6 +33,12 @@ struct Tang {
   static constexpr int t2 = (NDIM == 3) ? ((AX == 2) ? 1 : 2) : -1;
 };
 
+// The elements of a record that a thread takes: first, first + step, ... (one
+// workgroup per record, or several where a launch has few records).
+struct Part {
+  int first, step;
+};
+
 __device__ __forceinline__ double mm(double a, double b) {
   if (a > 0.0 && b > 0.0) return a < b ? a : b;
   if (a < 0.0 && b < 0.0) return a > b ? a : b;
@@ -37,20 +46,19 @@ __device__ __forceinline__ double mm(double a, double b) {
 }
 
 template <typename T, int NDIM, int NV, int N, int ax>
-__device__ void srl_record(const MeshDev &M, T *u, int32_t a, int32_t b) {
+__device__ __forceinline__ void srl_record(int g, T *u, Part pt, int32_t a, int32_t b) {
   constexpr int N2 = (NDIM == 3) ? N : 1;
-  const Geo<NDIM> G(N, M.g);
-  const int g = M.g;
+  const Geo<NDIM> G(N, g);
   constexpr int t1 = Tang<NDIM, ax>::t1, t2 = Tang<NDIM, ax>::t2;
   const int64_t bel = G.sv * NV;
   const int total = 2 * NV * N2 * N * g;
   constexpr int B = 8;  // elements in flight per thread: loads first, then stores
-  for (int e0 = threadIdx.x; e0 < total; e0 += B * blockDim.x) {
+  for (int e0 = pt.first; e0 < total; e0 += B * pt.step) {
     T val[B];
     int64_t dsto[B];
 #pragma unroll
     for (int q = 0; q < B; q++) {
-      const int e = e0 + q * blockDim.x;
+      const int e = e0 + q * pt.step;
       dsto[q] = -1;
       if (e >= total) continue;
       int l, p1, p2, v, side, r = e;
@@ -98,7 +106,7 @@ struct Pair {
 };
 
 template <typename T, int NDIM, int NV, int N>
-__device__ void srl_record_x2(const MeshDev &M, T *u, int32_t a, int32_t b) {
+__device__ __forceinline__ void srl_record_x2(T *u, Part pt, int32_t a, int32_t b) {
   using PT = typename Pair<T>::type;
   constexpr int N2 = (NDIM == 3) ? N : 1;
   constexpr int P = N + 4;
@@ -107,12 +115,12 @@ __device__ void srl_record_x2(const MeshDev &M, T *u, int32_t a, int32_t b) {
   constexpr int64_t BEL = SV * NV;
   constexpr int total = 2 * NV * N2 * N;
   constexpr int B = 4;  // pairs in flight per thread (8 values): loads first, then stores
-  for (int e0 = threadIdx.x; e0 < total; e0 += B * blockDim.x) {
+  for (int e0 = pt.first; e0 < total; e0 += B * pt.step) {
     PT val[B];
     int64_t dsto[B];
 #pragma unroll
     for (int q = 0; q < B; q++) {
-      const int e = e0 + q * blockDim.x;
+      const int e = e0 + q * pt.step;
       dsto[q] = -1;
       if (e >= total) continue;
       int r = e;
@@ -168,16 +176,15 @@ __device__ __forceinline__ double fine_mean(const T *uq, const Geo<NDIM> &G, con
 }
 
 template <typename T, int NDIM, int NV, int N, int ax>
-__device__ void f2c_record(const MeshDev &M, T *u, int side, int32_t cb, int32_t q, int32_t h) {
+__device__ __forceinline__ void f2c_record(int g, T *u, Part pt, int side, int32_t cb, int32_t q, int32_t h) {
   constexpr int H = N / 2;
   constexpr int H2 = (NDIM == 3) ? H : 1;
-  const Geo<NDIM> G(N, M.g);
-  const int g = M.g;
+  const Geo<NDIM> G(N, g);
   constexpr int t1 = Tang<NDIM, ax>::t1, t2 = Tang<NDIM, ax>::t2;
   const int bt1 = h & 1, bt2 = (h >> 1) & 1;
   const int64_t bel = G.sv * NV;
   const int total = NV * H2 * H * g;
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
+  for (int e = pt.first; e < total; e += pt.step) {
     int l, p1, p2, v, r = e;
     if (ax == 0) {
       l = r % g; r /= g;
@@ -241,11 +248,10 @@ __device__ __forceinline__ double prolong(const Stencil<T, NDIM> &s, const int s
 }
 
 template <typename T, int NDIM, int NV, int N, int ax>
-__device__ void c2f_record(const MeshDev &M, T *u, int side, int32_t q, int32_t cb, int32_t h) {
+__device__ __forceinline__ void c2f_record(int g, T *u, Part pt, int side, int32_t q, int32_t cb, int32_t h) {
   constexpr int N2 = (NDIM == 3) ? N : 1;
   constexpr int H = N / 2;
-  const Geo<NDIM> G(N, M.g);
-  const int g = M.g;
+  const Geo<NDIM> G(N, g);
   constexpr int t1 = Tang<NDIM, ax>::t1, t2 = Tang<NDIM, ax>::t2;
   const int bt1 = h & 1, bt2 = (h >> 1) & 1;
   const int64_t bel = G.sv * NV;
@@ -253,13 +259,13 @@ __device__ void c2f_record(const MeshDev &M, T *u, int side, int32_t q, int32_t 
   // elements in flight per thread, stencils first, then values: two in FP32;
   // in FP64 a second stencil would cost the ghost kernel a wave per SIMD
   constexpr int B = sizeof(T) == 4 ? 2 : 1;
-  for (int e0 = threadIdx.x; e0 < total; e0 += B * blockDim.x) {
+  for (int e0 = pt.first; e0 < total; e0 += B * pt.step) {
     Stencil<T, NDIM> st[B];
     int sg[B][3];
     int64_t dsto[B];
 #pragma unroll
     for (int k = 0; k < B; k++) {
-      const int e = e0 + k * blockDim.x;
+      const int e = e0 + k * pt.step;
       dsto[k] = -1;
       if (e >= total) continue;
       int l, p1, p2, v, r = e;
@@ -305,11 +311,11 @@ __device__ void c2f_record(const MeshDev &M, T *u, int side, int32_t q, int32_t 
 // stay live between the two passes (the cell coordinates are decoded again),
 // which keeps this routine from setting the ghost kernel's register count.
 template <typename T, int NDIM, int NV, int N, int ax>
-__device__ void bc_record(const MeshDev &M, T *u, int side, int64_t rec, int32_t b) {
+__device__ __forceinline__ void bc_record(const MeshDev &M, int g, T *u, Part pt, int side, int64_t rec, int32_t b) {
 #pragma clang fp contract(off)
   constexpr int N2 = (NDIM == 3) ? N : 1;
-  const Geo<NDIM> G(N, M.g);
-  const int g = M.g, f = 2 * ax + side;
+  const Geo<NDIM> G(N, g);
+  const int f = 2 * ax + side;
   constexpr int t1 = Tang<NDIM, ax>::t1, t2 = Tang<NDIM, ax>::t2;
   T *ub = u + (int64_t)b * G.sv * NV;
   const double dx = ldexp(M.dx0, -M.level[b]);
@@ -333,11 +339,11 @@ __device__ void bc_record(const MeshDev &M, T *u, int side, int64_t rec, int32_t
     v = r;
   };
   constexpr int B = 4;
-  for (int e0 = threadIdx.x; e0 < total; e0 += B * blockDim.x) {
+  for (int e0 = pt.first; e0 < total; e0 += B * pt.step) {
     double uin[B];
 #pragma unroll
     for (int q = 0; q < B; q++) {
-      const int e = e0 + q * blockDim.x;
+      const int e = e0 + q * pt.step;
       if (e >= total) continue;
       int l, p1, p2, v;
       decode(e, l, p1, p2, v);
@@ -349,7 +355,7 @@ __device__ void bc_record(const MeshDev &M, T *u, int side, int64_t rec, int32_t
     }
 #pragma unroll
     for (int q = 0; q < B; q++) {
-      const int e = e0 + q * blockDim.x;
+      const int e = e0 + q * pt.step;
       if (e >= total) continue;
       int l, p1, p2, v;
       decode(e, l, p1, p2, v);
@@ -378,24 +384,23 @@ struct Quad {  // one 16-byte chunk: W values of T (four FP32, two FP64)
 };
 
 template <typename T, int NDIM, int NV, int N, int ax>
-__device__ void srl_record_rows(const MeshDev &M, T *u, int32_t a, int32_t b) {
+__device__ __forceinline__ void srl_record_rows(int g, T *u, Part pt, int32_t a, int32_t b) {
   static_assert(ax >= 1 && ax < NDIM, "row copies serve the y and z faces");
   using VT = typename Quad<T>::type;
   constexpr int W = Quad<T>::W, NW = N / W;
   static_assert(N % W == 0, "rows hold whole 16-byte chunks");
   constexpr int N2 = (NDIM == 3) ? N : 1;
-  const Geo<NDIM> G(N, M.g);
-  const int g = M.g;
+  const Geo<NDIM> G(N, g);
   constexpr int t2 = Tang<NDIM, ax>::t2;
   const int64_t bel = G.sv * NV;
   const int total = 2 * NV * N2 * NW * g;
   constexpr int B = 4;  // chunks in flight per thread: loads first, then stores
-  for (int e0 = threadIdx.x; e0 < total; e0 += B * blockDim.x) {
+  for (int e0 = pt.first; e0 < total; e0 += B * pt.step) {
     VT val[B];
     int64_t dsto[B];
 #pragma unroll
     for (int q = 0; q < B; q++) {
-      const int e = e0 + q * blockDim.x;
+      const int e = e0 + q * pt.step;
       dsto[q] = -1;
       if (e >= total) continue;
       int l, p2, r = e;
@@ -426,9 +431,65 @@ __device__ void srl_record_rows(const MeshDev &M, T *u, int32_t a, int32_t b) {
   }
 }
 
-template <typename T, int NDIM, int NV, int N>
-__device__ void ghost_item(const MeshDev &M, int round, int64_t r, int which) {
-  T *u = (T *)M.s[role_buffer(which, M.cur)];
+// The descriptor fields that locate a record, read together before any of them
+// is used: read where they are needed, each branch waits for its own load (a
+// miss of the scalar cache is most of a microsecond in a launch that moves
+// little data).
+struct Locate {
+  int32_t cur, g, r1_srl, n_f2c, srl_first;
+  void *s[4];
+  const int32_t *sub, *srl, *f2c, *bc, *c2f;
+  int32_t off[3][5];  // starts of faces 1 .. 5: R1 SRL, F2C, BC; R2 C2F
+  // face of record r in offsets k: the number of faces that start at or before r
+  __device__ __forceinline__ int face(int k, int64_t r) const {
+    int f = 0;
+#pragma unroll
+    for (int q = 0; q < 5; q++) f += r >= off[k][q];
+    return f;
+  }
+};
+
+template <int ROUND>
+__device__ __forceinline__ Locate locate_fields(const MeshDev &M) {
+  Locate L;
+  L.cur = M.cur;
+  L.g = M.g;
+#pragma unroll
+  for (int q = 0; q < 4; q++) L.s[q] = M.s[q];
+  if constexpr (ROUND == 1) {
+    L.r1_srl = M.r1_srl;
+    L.n_f2c = M.pn[kF2C];
+    L.srl_first = M.srl_first;
+    L.sub = M.srl_sub;
+    L.srl = M.srl;
+    L.f2c = M.f2c;
+    L.bc = M.bc;
+#pragma unroll
+    for (int q = 0; q < 5; q++) {
+      L.off[0][q] = M.poff[kSRL][q + 1];
+      L.off[1][q] = M.poff[kF2C][q + 1];
+      L.off[2][q] = M.poff[kBC][q + 1];
+    }
+    asm volatile("" ::"s"(L.cur), "s"(L.g), "s"(L.s[0]), "s"(L.s[1]), "s"(L.s[2]), "s"(L.s[3]), "s"(L.r1_srl),
+                 "s"(L.n_f2c), "s"(L.srl_first), "s"(L.sub), "s"(L.srl), "s"(L.f2c), "s"(L.bc), "s"(L.off[0][0]),
+                 "s"(L.off[0][2]), "s"(L.off[0][4]), "s"(L.off[1][0]), "s"(L.off[1][2]), "s"(L.off[1][4]),
+                 "s"(L.off[2][0]), "s"(L.off[2][2]), "s"(L.off[2][4]));
+  } else {
+    L.c2f = M.c2f;
+#pragma unroll
+    for (int q = 0; q < 5; q++) L.off[0][q] = M.poff[kC2F][q + 1];
+    asm volatile("" ::"s"(L.cur), "s"(L.g), "s"(L.s[0]), "s"(L.s[1]), "s"(L.s[2]), "s"(L.s[3]), "s"(L.c2f),
+                 "s"(L.off[0][0]), "s"(L.off[0][2]), "s"(L.off[0][4]));
+  }
+  return L;
+}
+
+template <typename T, int NDIM, int NV, int ROUND, int N>
+__device__ __forceinline__ void ghost_item(const MeshDev &M, const Locate &L, int64_t r, int which, Part pt) {
+  const int ub = role_buffer(which, L.cur);
+  T *u = (T *)(ub == 0 ? L.s[0] : ub == 1 ? L.s[1] : ub == 2 ? L.s[2] : L.s[3]);
+  const int g = L.g;
+  int f;
   // the record's face f = 2 axis + side; the axis selects the routine
 #define F4_BY_AXIS(CALL)                           \
   switch (f >> 1) {                                \
@@ -436,72 +497,81 @@ __device__ void ghost_item(const MeshDev &M, int round, int64_t r, int which) {
     case 1: CALL(1); break;                        \
     default: if constexpr (NDIM == 3) CALL(2);     \
   }
-  if (round == 1) {
-    if (r < M.r1_srl) {
-      r = M.srl_sub ? M.srl_sub[r] : r + M.srl_first;
-      int f = 1;
-      while (r >= M.poff[kSRL][f + 1]) f += 2;
+  if constexpr (ROUND == 1) {
+    const int64_t n_srl = L.r1_srl, n_f2c = L.n_f2c;
+    if (r < n_srl) {
+      int32_t a, b;
+      if (L.sub) {
+        a = L.sub[3 * r];
+        b = L.sub[3 * r + 1];
+        f = L.sub[3 * r + 2];
+      } else {
+        r += L.srl_first;
+        a = L.srl[2 * r];
+        b = L.srl[2 * r + 1];
+        f = L.face(0, r);
+      }
 #define F4_SRL(A)                                                          \
   do {                                                                     \
     if constexpr ((A) > 0)                                                 \
-      srl_record_rows<T, NDIM, NV, N, A>(M, u, M.srl[2 * r], M.srl[2 * r + 1]); \
-    else if (M.g == 2)                                                     \
-      srl_record_x2<T, NDIM, NV, N>(M, u, M.srl[2 * r], M.srl[2 * r + 1]); \
+      srl_record_rows<T, NDIM, NV, N, A>(g, u, pt, a, b);                  \
+    else if (g == 2)                                                       \
+      srl_record_x2<T, NDIM, NV, N>(u, pt, a, b);                          \
     else                                                                   \
-      srl_record<T, NDIM, NV, N, A>(M, u, M.srl[2 * r], M.srl[2 * r + 1]); \
+      srl_record<T, NDIM, NV, N, A>(g, u, pt, a, b);                       \
   } while (0)
       F4_BY_AXIS(F4_SRL)
 #undef F4_SRL
-    } else if (r < M.r1_srl + M.pn[kF2C]) {
-      r -= M.r1_srl;
-      int f = 0;
-      while (r >= M.poff[kF2C][f + 1]) f++;
-#define F4_F2C(A) f2c_record<T, NDIM, NV, N, A>(M, u, f & 1, M.f2c[4 * r], M.f2c[4 * r + 1], M.f2c[4 * r + 2])
+    } else if (r < n_srl + n_f2c) {
+      r -= n_srl;
+      f = L.face(1, r);
+      const int32_t cb = L.f2c[4 * r], q = L.f2c[4 * r + 1], h = L.f2c[4 * r + 2];
+#define F4_F2C(A) f2c_record<T, NDIM, NV, N, A>(g, u, pt, f & 1, cb, q, h)
       F4_BY_AXIS(F4_F2C)
 #undef F4_F2C
     } else {
-      r -= M.r1_srl + M.pn[kF2C];
-      int f = 0;
-      while (r >= M.poff[kBC][f + 1]) f++;
-#define F4_BC(A) bc_record<T, NDIM, NV, N, A>(M, u, f & 1, r, M.bc[r])
+      r -= n_srl + n_f2c;
+      f = L.face(2, r);
+      const int32_t b = L.bc[r];
+#define F4_BC(A) bc_record<T, NDIM, NV, N, A>(M, g, u, pt, f & 1, r, b)
       F4_BY_AXIS(F4_BC)
 #undef F4_BC
     }
   } else {
-    int f = 0;
-    while (r >= M.poff[kC2F][f + 1]) f++;
-#define F4_C2F(A) c2f_record<T, NDIM, NV, N, A>(M, u, f & 1, M.c2f[3 * r], M.c2f[3 * r + 1], M.c2f[3 * r + 2])
+    f = L.face(0, r);
+    const int32_t q = L.c2f[3 * r], cb = L.c2f[3 * r + 1], h = L.c2f[3 * r + 2];
+#define F4_C2F(A) c2f_record<T, NDIM, NV, N, A>(g, u, pt, f & 1, q, cb, h)
     F4_BY_AXIS(F4_C2F)
 #undef F4_C2F
   }
 #undef F4_BY_AXIS
 }
 
-template <typename T, int NDIM, int NV>
-__global__ __launch_bounds__(256) void ghost_kernel(const MeshDev *__restrict__ meshes, int n_meshes,
-                                                    int64_t total, int round, int which) {
-  // one workgroup per record (grid = total): XCD-aware record order, as
-  // workgroup w runs on XCD w mod 8; XCD x takes the contiguous range of
-  // records [x q + min(x, r), ...) (total = 8 q + r), so consecutive records,
+template <typename T, int NDIM, int NV, int ROUND>
+__global__ __launch_bounds__(256) void ghost_kernel(const MeshDev *__restrict__ meshes, int n_meshes, int64_t total,
+                                                    int split, int which) {
+  // `split` workgroups per record (grid = total split): XCD-aware order, as
+  // workgroup w runs on XCD w mod 8; XCD x takes the contiguous range
+  // [x q + min(x, r), ...) (total split = 8 q + r), so consecutive records,
   // which touch the same blocks (the +x copies of (a, b) and (b, c) both read
-  // rows of b), share that XCD's L2.  A bijection onto 0 .. total-1.
-  const bool one_each = (int64_t)gridDim.x == total;
-  const int64_t xq = total / 8, xr = total % 8, xid = blockIdx.x % 8;
-  for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
-    const int64_t item = one_each ? xid * xq + (xid < xr ? xid : xr) + w / 8 : w;
-    int lo = 0, hi = n_meshes - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      const int64_t b = round == 1 ? meshes[mid].r1_begin : meshes[mid].r2_begin;
-      if (b <= item) lo = mid; else hi = mid - 1;
-    }
-    const MeshDev &M = meshes[lo];
-    const int64_t r = item - (round == 1 ? M.r1_begin : M.r2_begin);
-    switch (M.N) {
-      case 8: ghost_item<T, NDIM, NV, 8>(M, round, r, which); break;
-      case 16: ghost_item<T, NDIM, NV, 16>(M, round, r, which); break;
-      default: ghost_item<T, NDIM, NV, 32>(M, round, r, which); break;
-    }
+  // rows of b), share that XCD's L2.  A bijection onto 0 .. total split - 1.
+  const int64_t all = total * split, xq = all / 8, xr = all % 8, xid = blockIdx.x % 8;
+  const int64_t w = xid * xq + (xid < xr ? xid : xr) + blockIdx.x / 8;
+  const int64_t item = w / split;
+  const Part pt{(int)(w % split) * (int)blockDim.x + (int)threadIdx.x, split * (int)blockDim.x};
+  int lo = 0, hi = n_meshes - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    const int64_t b = ROUND == 1 ? meshes[mid].r1_begin : meshes[mid].r2_begin;
+    if (b <= item) lo = mid; else hi = mid - 1;
+  }
+  const MeshDev &M = meshes[lo];
+  const int64_t r = item - (ROUND == 1 ? M.r1_begin : M.r2_begin);
+  const Locate L = locate_fields<ROUND>(M);
+  switch (M.N) {
+    case 8: ghost_item<T, NDIM, NV, ROUND, 8>(M, L, r, which, pt); break;
+    case 16: ghost_item<T, NDIM, NV, ROUND, 16>(M, L, r, which, pt); break;
+    default: ghost_item<T, NDIM, NV, ROUND, 32>(M, L, r, which, pt); break;
   }
 }
 
@@ -594,10 +664,21 @@ hipError_t launch_srl_x_blocks(const MeshDev *d_mesh, int64_t nblocks, int which
 }
 
 hipError_t launch_ghost(const MeshDev *d_meshes, int n_meshes, int64_t total, int round, int which,
-                        int ndim, bool f64, int grid, hipStream_t s, int nv) {
+                        int ndim, bool f64, int block_n, int n_ghost, hipStream_t s, int nv) {
   if (total <= 0) return hipSuccess;
-  const unsigned nblk = (unsigned)((grid > 0 && grid < total) ? grid : total);
-#define F4_GHOST(T, D, V) ghost_kernel<T, D, V><<<nblk, 256, 0, s>>>(d_meshes, n_meshes, total, round, which)
+  // A record's elements take several rounds of one workgroup (an FP64 16^3
+  // prolongation: ten), each as long as a load from memory.  Launches of few
+  // records take more workgroups per record, up to eight per CU in all.  The
+  // walls of 225 16^2 columns (450 records): 14.6 us with one workgroup each,
+  // 11.7 us; what is left is the launch and four dependent loads.
+  const int64_t face = (int64_t)nv * n_ghost * (ndim == 3 ? block_n * block_n : block_n);
+  const int64_t split = std::max<int64_t>(1, std::min<int64_t>((face + 511) / 512, 2048 / total));
+  const unsigned nblk = (unsigned)(total * split);
+#define F4_GHOST(T, D, V)                                                                                     \
+  do {                                                                                                        \
+    if (round == 1) ghost_kernel<T, D, V, 1><<<nblk, 256, 0, s>>>(d_meshes, n_meshes, total, (int)split, which); \
+    else ghost_kernel<T, D, V, 2><<<nblk, 256, 0, s>>>(d_meshes, n_meshes, total, (int)split, which);         \
+  } while (0)
   if (nv == 1) {  // scalar advection
     if (f64) {
       if (ndim == 3) F4_GHOST(double, 3, 1);

@@ -230,11 +230,18 @@ __global__ void srl_need_kernel(const int32_t *srl, int64_t n_srl, const int8_t 
   if (r < n_srl) need[r] = (coarse[srl[2 * r]] | coarse[srl[2 * r + 1]]) ? 1 : 0;
 }
 
-// need[] holds the exclusive prefix sums of the flags (recomputed here)
+// need[] holds the exclusive prefix sums of the flags (recomputed here); y0 and
+// z0: the first records of the y and z faces.  sub: (a, b, face) per record
 __global__ void srl_compact_kernel(const int32_t *srl, int64_t n_srl, const int8_t *coarse, const int32_t *pos,
-                                   int32_t *sub) {
+                                   int32_t y0, int32_t z0, int32_t *sub) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n_srl && (coarse[srl[2 * r]] | coarse[srl[2 * r + 1]])) sub[pos[r]] = (int32_t)r;
+  if (r >= n_srl) return;
+  const int32_t a = srl[2 * r], b = srl[2 * r + 1];
+  if (!(coarse[a] | coarse[b])) return;
+  int32_t *o = sub + 3 * (int64_t)pos[r];
+  o[0] = a;
+  o[1] = b;
+  o[2] = 1 + 2 * ((r >= y0) + (r >= z0));
 }
 
 static foap4_status ensure(foap4_mesh *m, void **p, size_t &cap, size_t bytes) {
@@ -330,9 +337,9 @@ foap4_status build_pattern(foap4_mesh *m) {
     int32_t n_sub = 0;
     F4_HIP(m, hipMemcpyAsync(&n_sub, P.tot + rows + 1, 4, hipMemcpyDeviceToHost, s));
     F4_HIP(m, hipStreamSynchronize(s));
-    if ((st = ensure(m, (void **)&P.srl_c2f, P.cap_srl_c2f, (size_t)n_sub * 4)) != FOAP4_OK) return st;
+    if ((st = ensure(m, (void **)&P.srl_c2f, P.cap_srl_c2f, (size_t)n_sub * 12)) != FOAP4_OK) return st;
     srl_compact_kernel<<<(unsigned)((P.n[kSRL] + 255) / 256), 256, 0, s>>>(P.srl, P.n[kSRL], coarse, pos,
-                                                                            P.srl_c2f);
+                                                                            P.off[kSRL][2], P.off[kSRL][4], P.srl_c2f);
     F4_HIP(m, hipGetLastError());
     P.n_srl_c2f = n_sub;
   }
