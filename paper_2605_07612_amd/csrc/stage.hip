@@ -581,9 +581,14 @@ __device__ __forceinline__ int64_t item_of(int64_t w, int64_t it, int64_t grid, 
 // registers, which ran faster than 3 waves without spills); the mixed-size
 // FP32 kernel 3 (its LDS allows 3 workgroups per CU; at 168 registers it
 // spills a little and ran ~14 % faster than at 2 waves); FP64 kernels keep
-// what their registers allow.
+// what their registers allow, but RK4's last sub-step on 16^3 and 32^3 blocks,
+// at 261 registers and one wave, is held to the 2 waves that its LDS allows
+// (256^3 cells, two RK4 steps: minmod 5170 -> 4810 us, van Leer 5994 -> 5512;
+// given to the other sub-steps as well, the hint costs their schedule 2-4 %).
 template <typename T, int NM, int STG = 2>
-constexpr int stage_waves() { return sizeof(T) == 4 ? (NM != 7 ? 4 : 3) : 1; }
+constexpr int stage_waves() {
+  return sizeof(T) == 4 ? (NM != 7 ? 4 : 3) : (STG == 4 && (NM == 2 || NM == 4) ? 2 : 1);
+}
 
 // NM: bit mask of the block sizes present (1: N = 8, 2: N = 16, 4: N = 32)
 // STG: the Heun stage (compiled separately: stage 1 needs no U^n stream and
