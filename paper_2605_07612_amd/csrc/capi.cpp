@@ -507,7 +507,7 @@ foap4_status foap4_step(foap4_mesh *m, int32_t n_steps, double *t_out, double *d
         if ((st = fill_step(m, subs[k].deriv)) != FOAP4_OK) return st;
         const int form = substep_form(subs[k]);
         F4_HIP(m, mesh_stage(m, items, form, subs[k]));
-        F4_HIP(m, launch_fluxfix(m->d_dev + 1, ndim, m->nvar, f64, m->pat.n_fix, form, m->stream, subs[k]));
+        F4_HIP(m, launch_fluxfix(m->d_dev + 1, ndim, m->nvar, f64, m->d.block_n, m->pat.n_fix, form, m->stream, subs[k]));
       }
       F4_HIP(m, launch_finalize(m->d_dev, 1, 1, m->stream));
     }
@@ -539,10 +539,10 @@ foap4_status foap4_step(foap4_mesh *m, int32_t n_steps, double *t_out, double *d
     } else {
       F4_HIP(m, mesh_stage(m, items, 1));
     }
-    F4_HIP(m, launch_fluxfix(m->d_dev + 1, ndim, m->nvar, f64, m->pat.n_fix, 1, m->stream));
+    F4_HIP(m, launch_fluxfix(m->d_dev + 1, ndim, m->nvar, f64, m->d.block_n, m->pat.n_fix, 1, m->stream));
     if ((st = fill_step(m, 1)) != FOAP4_OK) return st;
     F4_HIP(m, mesh_stage(m, items, 2));
-    F4_HIP(m, launch_fluxfix(m->d_dev + 1, ndim, m->nvar, f64, m->pat.n_fix, 2, m->stream));
+    F4_HIP(m, launch_fluxfix(m->d_dev + 1, ndim, m->nvar, f64, m->d.block_n, m->pat.n_fix, 2, m->stream));
     F4_HIP(m, launch_finalize(m->d_dev, 1, 1, m->stream));
   }
   m->steps_done += n_steps;
@@ -872,7 +872,8 @@ static hipError_t batch_enqueue_step(foap4_batch *b, hipStream_t s) {
     if ((e = batch_stage(b, form, stage_grid(b, 2), s, subs[k])) != hipSuccess) return e;
     for (int i = 0; i < n; i++)
       if (b->meshes[i]->pat.n_fix > 0 &&
-          (e = launch_fluxfix(b->d_devs + i, b->ndim, b->nv, b->f64, b->meshes[i]->pat.n_fix, form, s, subs[k])) != hipSuccess)
+          (e = launch_fluxfix(b->d_devs + i, b->ndim, b->nv, b->f64, b->meshes[i]->d.block_n,
+                            b->meshes[i]->pat.n_fix, form, s, subs[k])) != hipSuccess)
         return e;
   }
   if (nsub) return launch_finalize(b->d_devs, n, 1, s);
@@ -885,7 +886,8 @@ static hipError_t batch_enqueue_step(foap4_batch *b, hipStream_t s) {
     if ((e = batch_stage(b, stage, grid, s)) != hipSuccess) return e;
     for (int i = 0; i < n; i++)
       if (b->meshes[i]->pat.n_fix > 0 &&
-          (e = launch_fluxfix(b->d_devs + i, b->ndim, b->nv, b->f64, b->meshes[i]->pat.n_fix, stage, s)) != hipSuccess)
+          (e = launch_fluxfix(b->d_devs + i, b->ndim, b->nv, b->f64, b->meshes[i]->d.block_n,
+                            b->meshes[i]->pat.n_fix, stage, s)) != hipSuccess)
         return e;
   }
   return launch_finalize(b->d_devs, n, 1, s);
@@ -1042,7 +1044,8 @@ foap4_status foap4_batch_phase_times(foap4_batch *b, int32_t n_steps, double *ou
       B_HIP(b, hipEventRecord(ev[++k], s));
       for (int i = 0; i < n; i++)
         if (b->meshes[i]->pat.n_fix > 0)
-          B_HIP(b, launch_fluxfix(b->d_devs + i, b->ndim, b->nv, b->f64, b->meshes[i]->pat.n_fix, stage, s));
+          B_HIP(b, launch_fluxfix(b->d_devs + i, b->ndim, b->nv, b->f64, b->meshes[i]->d.block_n,
+                            b->meshes[i]->pat.n_fix, stage, s));
       B_HIP(b, hipEventRecord(ev[++k], s));
     }
     B_HIP(b, launch_finalize(b->d_devs, n, 1, s));

@@ -286,8 +286,8 @@ inline int nmask_of(int N) { return N == 8 ? 1 : (N == 16 ? 2 : 4); }
 // reduce.hip
 hipError_t launch_dt_full(const foap4_mesh *m, hipStream_t s);
 hipError_t launch_finalize(const MeshDev *d_meshes, int n_meshes, int advance, hipStream_t s);
-hipError_t launch_fluxfix(const MeshDev *d_mesh, int ndim, int nv, bool f64, int n_fix, int stage, hipStream_t s,
-                          const SubStep &ss = SubStep{});
+hipError_t launch_fluxfix(const MeshDev *d_mesh, int ndim, int nv, bool f64, int block_n, int n_fix, int stage,
+                          hipStream_t s, const SubStep &ss = SubStep{});
 hipError_t launch_totals(const foap4_mesh *m, double *d_part, double *d_out, hipStream_t s);
 // The allocation-free totals: a fixed device array of kNoAllocScratchDoubles
 // FP64 values (2 MiB) per GPU, looked up once per device (with that device

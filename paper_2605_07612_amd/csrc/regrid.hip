@@ -7,7 +7,7 @@ namespace f4 {
 // the operation order of the definition and no contraction, so that the
 // flags equal a plain evaluation bit for bit.  One workgroup per block.
 template <typename T, int NDIM, int NV>
-__global__ __launch_bounds__(256) void lohner_kernel(const MeshDev *__restrict__ Mp, double cr2, double cd2,
+__global__ __launch_bounds__(1024) void lohner_kernel(const MeshDev *__restrict__ Mp, double cr2, double cd2,
                                                      double eps, double eps_abs, int8_t *flags,
                                                      const int8_t *skip) {
 #pragma clang fp contract(off)
@@ -41,102 +41,131 @@ __global__ __launch_bounds__(256) void lohner_kernel(const MeshDev *__restrict__
   if (threadIdx.x == 0) flags[b] = r ? 1 : (dall ? -1 : 0);
 }
 
-// One workgroup per new block: map[n] = (op, src, arg) with op 0 copy old
-// block src, op 1 prolong child arg (bits x + 2y + 4z) of old block src with
-// limited slopes (old ghosts filled), op 2 restrict old children src..src+2^d-1.
-template <typename T, int NDIM, int NV>
-__global__ __launch_bounds__(256) void remap_kernel(const T *__restrict__ uold, T *unew, const int32_t *map, int N,
-                                                    int g) {
+// map[n] = (op, src, arg) of every new block n: op 0 copy old block src, op 1
+// prolong child arg (bits x + 2y + 4z) of old block src with limited slopes
+// (old ghosts filled), op 2 restrict old children src .. src + 2^d - 1.
+//
+// A workgroup takes one variable of one new block, or one of `parts` parts of
+// it, and each thread moves what lies together: 16 bytes of a copied plane, the
+// two fine cells that share a coarse cell along x, the four pairs of fine cells
+// under a coarse one.  With one workgroup per block and one value per thread and
+// round (80 rounds of a load each for an FP64 16^3 block) it was bound by load
+// latency: 216 FP64 16^3 blocks, a ball of them refined and coarsened again: 114
+// us a launch, 30 us now.
+template <typename T, int NDIM, int NV, int N>
+__device__ __forceinline__ void remap_block(const T *__restrict__ uold, T *unew, int op, int64_t src, int arg,
+                                            int64_t n, int v, int g, int first, int step) {
   // FP64 in the operation order of the definitions, no contraction (the
   // prolonged value u_P + corr / 4 stays bit-exact when corr / 4 is subnormal)
 #pragma clang fp contract(off)
-  const int64_t n = blockIdx.x;
-  const int P = N + 2 * g, H = N / 2;
+  typedef T Pair __attribute__((ext_vector_type(2)));
+  constexpr int H = N / 2, CELLS = NDIM == 3 ? N * N * N : N * N;
+  const int P = N + 2 * g;
   const int64_t sv = (NDIM == 3) ? (int64_t)P * P * P : (int64_t)P * P;
   const int64_t bel = sv * NV;
-  const int op = map[3 * n], src = map[3 * n + 1], arg = map[3 * n + 2];
-  const int cells = (NDIM == 3) ? N * N * N : N * N;
-  auto at = [&](const int c[3]) -> int64_t { return cell_off<NDIM>(c[0], c[1], c[2], N, g); };
-  for (int e = threadIdx.x; e < NV * cells; e += blockDim.x) {
-    const int v = e / cells, c0 = e % cells;
-    const int c[3] = {c0 % N, (c0 / N) % N, (NDIM == 3) ? c0 / (N * N) : 0};
-    double val;
-    if (op == 0) {
-      val = uold[(int64_t)src * bel + v * sv + at(c)];
-    } else if (op == 1) {
-      const T *uc = uold + (int64_t)src * bel + v * sv;
-      int Pc[3] = {0, 0, 0}, sig[3] = {0, 0, 0};
+  auto at = [&](int i, int j, int k) -> int { return cell_off<NDIM>(i, j, k, N, g); };
+  T *un = unew + n * bel + v * sv;
+  if (op == 0) {
+    // an interior plane is N^2 contiguous values, and every offset is a
+    // multiple of 16 bytes: N is a multiple of 8, P and so the strides of a
+    // variable and a block are even (2D: P^2 a multiple of 4)
+    constexpr int W = 16 / (int)sizeof(T);
+    typedef T Vec __attribute__((ext_vector_type(W)));
+    const T *uo = uold + src * bel + v * sv;
+    constexpr int B = 4;  // loads in flight per thread
+    for (int e0 = first; e0 < CELLS / W; e0 += B * step) {
+      Vec val[B];
 #pragma unroll
-      for (int d = 0; d < NDIM; d++) {
-        Pc[d] = ((arg >> d) & 1) * H + (c[d] >> 1);
-        sig[d] = (c[d] & 1) ? 1 : -1;
+      for (int q = 0; q < B; q++) {
+        const int c = (e0 + q * step) * W;
+        if (c < CELLS) val[q] = *(const Vec *)(uo + at(0, 0, c / (N * N)) + c % (N * N));
       }
-      const double up = uc[at(Pc)];
-      double corr = 0.0;
 #pragma unroll
-      for (int d = 0; d < NDIM; d++) {
-        int lo[3] = {Pc[0], Pc[1], Pc[2]}, hi[3] = {Pc[0], Pc[1], Pc[2]};
-        lo[d] -= 1;
-        hi[d] += 1;
-        const double a = up - (double)uc[at(lo)], bb = (double)uc[at(hi)] - up;
-        double delta = 0.0;
-        if (a > 0.0 && bb > 0.0) delta = a < bb ? a : bb;
-        else if (a < 0.0 && bb < 0.0) delta = a > bb ? a : bb;
-        const double term = sig[d] > 0 ? delta : -delta;
-        corr = (d == 0) ? term : corr + term;
-      }
-      val = up + 0.25 * corr;
-    } else {
-      int ch = 0, base[3] = {0, 0, 0};
-#pragma unroll
-      for (int d = 0; d < NDIM; d++) {
-        const int bit = c[d] >= H;
-        ch |= bit << d;
-        base[d] = 2 * (c[d] - bit * H);
-      }
-      const T *uq = uold + (int64_t)(src + ch) * bel + v * sv;
-      if (NDIM == 2) {
-        int q[3] = {base[0], base[1], 0};
-        const double f00 = uq[at(q)];
-        q[0]++; const double f10 = uq[at(q)];
-        q[1]++; const double f11 = uq[at(q)];
-        q[0]--; const double f01 = uq[at(q)];
-        val = ((f00 + f10) + (f01 + f11)) * 0.25;
-      } else {
-        double f[2][2][2];
-        for (int oz = 0; oz < 2; oz++)
-          for (int oy = 0; oy < 2; oy++)
-            for (int ox = 0; ox < 2; ox++) {
-              const int q[3] = {base[0] + ox, base[1] + oy, base[2] + oz};
-              f[oz][oy][ox] = uq[at(q)];
-            }
-        const double a0 = f[0][0][0] + f[0][0][1], a1 = f[0][1][0] + f[0][1][1];
-        const double a2 = f[1][0][0] + f[1][0][1], a3 = f[1][1][0] + f[1][1][1];
-        val = ((a0 + a1) + (a2 + a3)) * 0.125;
+      for (int q = 0; q < B; q++) {
+        const int c = (e0 + q * step) * W;
+        if (c < CELLS) *(Vec *)(un + at(0, 0, c / (N * N)) + c % (N * N)) = val[q];
       }
     }
-    unew[n * bel + v * sv + at(c)] = (T)val;
+  } else if (op == 1) {
+    const T *uc = uold + src * bel + v * sv;
+    for (int e = first; e < CELLS / 2; e += step) {
+      const int hi = e % H, j = (e / H) % N, k = NDIM == 3 ? e / (H * N) : 0;
+      const int pc[3] = {(arg & 1) * H + hi, ((arg >> 1) & 1) * H + (j >> 1),
+                         NDIM == 3 ? ((arg >> 2) & 1) * H + (k >> 1) : 0};
+      const double up = uc[at(pc[0], pc[1], pc[2])];
+      double delta[NDIM];
+#pragma unroll
+      for (int d = 0; d < NDIM; d++) {
+        const int dx = d == 0, dy = d == 1, dz = d == 2;
+        const double a = up - (double)uc[at(pc[0] - dx, pc[1] - dy, pc[2] - dz)];
+        const double bb = (double)uc[at(pc[0] + dx, pc[1] + dy, pc[2] + dz)] - up;
+        delta[d] = 0.0;
+        if (a > 0.0 && bb > 0.0) delta[d] = a < bb ? a : bb;
+        else if (a < 0.0 && bb < 0.0) delta[d] = a > bb ? a : bb;
+      }
+      Pair out;
+#pragma unroll
+      for (int s = 0; s < 2; s++) {
+        double corr = s ? delta[0] : -delta[0];
+        corr = corr + ((j & 1) ? delta[1] : -delta[1]);
+        if constexpr (NDIM == 3) corr = corr + ((k & 1) ? delta[2] : -delta[2]);
+        out[s] = (T)(up + 0.25 * corr);
+      }
+      *(Pair *)(un + at(2 * hi, j, k)) = out;
+    }
+  } else {
+    for (int e = first; e < CELLS; e += step) {
+      const int i = e % N, j = (e / N) % N, k = NDIM == 3 ? e / (N * N) : 0;
+      const int bx = i >= H, by = j >= H, bz = NDIM == 3 ? k >= H : 0;
+      const int x = 2 * (i - bx * H), y = 2 * (j - by * H), z = NDIM == 3 ? 2 * (k - bz * H) : 0;
+      const T *uq = uold + (src + (bx + 2 * by + 4 * bz)) * bel + v * sv;
+      auto pair = [&](int yy, int zz) -> Pair { return *(const Pair *)(uq + at(x, yy, zz)); };
+      double val;
+      if constexpr (NDIM == 2) {
+        const Pair f0 = pair(y, 0), f1 = pair(y + 1, 0);
+        val = (((double)f0[0] + (double)f0[1]) + ((double)f1[0] + (double)f1[1])) * 0.25;
+      } else {
+        const Pair f0 = pair(y, z), f1 = pair(y + 1, z), f2 = pair(y, z + 1), f3 = pair(y + 1, z + 1);
+        const double a0 = (double)f0[0] + (double)f0[1], a1 = (double)f1[0] + (double)f1[1];
+        const double a2 = (double)f2[0] + (double)f2[1], a3 = (double)f3[0] + (double)f3[1];
+        val = ((a0 + a1) + (a2 + a3)) * 0.125;
+      }
+      un[at(i, j, k)] = (T)val;
+    }
+  }
+}
+
+template <typename T, int NDIM, int NV>
+__global__ __launch_bounds__(256) void remap_kernel(const T *__restrict__ uold, T *unew, const int32_t *map, int N,
+                                                    int g, int parts) {
+  const int64_t item = blockIdx.x / parts, n = item / NV;
+  const int v = (int)(item % NV), first = (int)(blockIdx.x % parts) * 256 + (int)threadIdx.x, step = parts * 256;
+  const int op = map[3 * n], src = map[3 * n + 1], arg = map[3 * n + 2];
+  switch (N) {
+    case 8: remap_block<T, NDIM, NV, 8>(uold, unew, op, src, arg, n, v, g, first, step); break;
+    case 16: remap_block<T, NDIM, NV, 16>(uold, unew, op, src, arg, n, v, g, first, step); break;
+    default: remap_block<T, NDIM, NV, 32>(uold, unew, op, src, arg, n, v, g, first, step); break;
   }
 }
 
 // Instantiation by (element type, dimension, variables): the Euler system
 // (ndim + 2 variables) or scalar advection (one).
-#define F4_BY_TYPE(KERNEL, T_, GRID, ...)                                                 \
+#define F4_BY_TYPE(KERNEL, T_, GRID, THREADS, ...)                                                 \
   do {                                                                                    \
     if (f64) {                                                                            \
       using T_ = double;                                                                  \
       if (nv == 1) {                                                                      \
-        if (ndim == 3) KERNEL<T_, 3, 1><<<(GRID), 256, 0, s>>>(__VA_ARGS__);              \
-        else KERNEL<T_, 2, 1><<<(GRID), 256, 0, s>>>(__VA_ARGS__);                        \
-      } else if (ndim == 3) KERNEL<T_, 3, 5><<<(GRID), 256, 0, s>>>(__VA_ARGS__);         \
-      else KERNEL<T_, 2, 4><<<(GRID), 256, 0, s>>>(__VA_ARGS__);                          \
+        if (ndim == 3) KERNEL<T_, 3, 1><<<(GRID), (THREADS), 0, s>>>(__VA_ARGS__);              \
+        else KERNEL<T_, 2, 1><<<(GRID), (THREADS), 0, s>>>(__VA_ARGS__);                        \
+      } else if (ndim == 3) KERNEL<T_, 3, 5><<<(GRID), (THREADS), 0, s>>>(__VA_ARGS__);         \
+      else KERNEL<T_, 2, 4><<<(GRID), (THREADS), 0, s>>>(__VA_ARGS__);                          \
     } else {                                                                              \
       using T_ = float;                                                                   \
       if (nv == 1) {                                                                      \
-        if (ndim == 3) KERNEL<T_, 3, 1><<<(GRID), 256, 0, s>>>(__VA_ARGS__);              \
-        else KERNEL<T_, 2, 1><<<(GRID), 256, 0, s>>>(__VA_ARGS__);                        \
-      } else if (ndim == 3) KERNEL<T_, 3, 5><<<(GRID), 256, 0, s>>>(__VA_ARGS__);         \
-      else KERNEL<T_, 2, 4><<<(GRID), 256, 0, s>>>(__VA_ARGS__);                          \
+        if (ndim == 3) KERNEL<T_, 3, 1><<<(GRID), (THREADS), 0, s>>>(__VA_ARGS__);              \
+        else KERNEL<T_, 2, 1><<<(GRID), (THREADS), 0, s>>>(__VA_ARGS__);                        \
+      } else if (ndim == 3) KERNEL<T_, 3, 5><<<(GRID), (THREADS), 0, s>>>(__VA_ARGS__);         \
+      else KERNEL<T_, 2, 4><<<(GRID), (THREADS), 0, s>>>(__VA_ARGS__);                          \
     }                                                                                     \
   } while (0)
 
@@ -147,7 +176,10 @@ hipError_t launch_lohner(const foap4_mesh *m, int8_t *d_flags, const int8_t *ski
   const double cr2 = cr * cr, cd2 = cd * cd, eps = 1e-2, eps_abs = 1e-10;
   const bool f64 = m->d.prec == FOAP4_F64;
   const int ndim = m->d.ndim, nv = m->nvar;
-  F4_BY_TYPE(lohner_kernel, T, (unsigned)nb, m->d_dev, cr2, cd2, eps, eps_abs, d_flags, skip);
+  // at most four cells a thread but for 32^3 blocks: each round is a load's latency
+  const int cells = ndim == 3 ? m->d.block_n * m->d.block_n * m->d.block_n : m->d.block_n * m->d.block_n;
+  const int threads = cells > 1024 ? 1024 : 256;
+  F4_BY_TYPE(lohner_kernel, T, (unsigned)nb, threads, m->d_dev, cr2, cd2, eps, eps_abs, d_flags, skip);
   return hipGetLastError();
 }
 
@@ -157,7 +189,9 @@ hipError_t launch_remap(const foap4_mesh *m, const void *src_state, void *dst_st
   const bool f64 = m->d.prec == FOAP4_F64;
   const int N = m->d.block_n, g = m->d.n_ghost;
   const int ndim = m->d.ndim, nv = m->nvar;
-  F4_BY_TYPE(remap_kernel, T, (unsigned)nb_new, (const T *)src_state, (T *)dst_state, d_map, N, g);
+  const int parts = (ndim == 3 ? N * N * N : N * N) > 2048 ? (N == 32 ? 16 : 2) : 1;  // at most 8 cells a thread
+  F4_BY_TYPE(remap_kernel, T, (unsigned)(nb_new * nv * parts), 256, (const T *)src_state, (T *)dst_state, d_map, N, g,
+             parts);
   return hipGetLastError();
 }
 
