@@ -140,22 +140,24 @@ foap4_status upload_dev(foap4_mesh *m) {
   return FOAP4_OK;
 }
 
+// Copies the leaf table to the device: keys, levels and coordinates in one
+// array and one copy.  Not waited for (h_leaf stays): the pattern build, which
+// follows every upload, synchronizes.
 static foap4_status upload_leaves(foap4_mesh *m) {
   const size_t nb = m->topo.leaves.size();
-  std::vector<int32_t> lev(nb), gc(3 * nb);
-  std::vector<uint64_t> keys(nb);
+  m->h_leaf.resize(24 * nb);
+  uint64_t *keys = (uint64_t *)m->h_leaf.data();
+  int32_t *lev = (int32_t *)(keys + nb), *gc = lev + nb;
   for (size_t i = 0; i < nb; i++) {
     const Leaf &L = m->topo.leaves[i];
+    keys[i] = m->topo.key(L);
     lev[i] = L.level;
     for (int d = 0; d < 3; d++) gc[3 * i + d] = L.g[d];
-    keys[i] = m->topo.key(L);
   }
-  if (nb) {
-    F4_HIP(m, hipMemcpyAsync(m->d_level, lev.data(), nb * 4, hipMemcpyHostToDevice, m->stream));
-    F4_HIP(m, hipMemcpyAsync(m->d_gc, gc.data(), nb * 12, hipMemcpyHostToDevice, m->stream));
-    F4_HIP(m, hipMemcpyAsync(m->d_keys, keys.data(), nb * 8, hipMemcpyHostToDevice, m->stream));
-  }
-  F4_HIP(m, hipStreamSynchronize(m->stream));
+  m->d_keys = (uint64_t *)m->d_leaf;
+  m->d_level = (int32_t *)(m->d_keys + nb);
+  m->d_gc = m->d_level + nb;
+  if (nb) F4_HIP(m, hipMemcpyAsync(m->d_leaf, m->h_leaf.data(), 24 * nb, hipMemcpyHostToDevice, m->stream));
   return FOAP4_OK;
 }
 
@@ -325,13 +327,11 @@ foap4_status foap4_mesh_create(const foap4_mesh_desc *desc, void *state0, void *
     return s;
   };
   const size_t cap = (size_t)d.max_blocks;
-  if (hipMalloc((void **)&m->d_level, cap * 4) != hipSuccess || hipMalloc((void **)&m->d_gc, cap * 12) != hipSuccess ||
-      hipMalloc((void **)&m->d_keys, cap * 8) != hipSuccess || hipMalloc((void **)&m->d_scal, kNScal * 8) != hipSuccess ||
+  if (hipMalloc(&m->d_leaf, cap * 24) != hipSuccess || hipMalloc((void **)&m->d_scal, kNScal * 8) != hipSuccess ||
       hipMalloc((void **)&m->d_dev, 2 * sizeof(MeshDev)) != hipSuccess) {
     m->err = "device allocation failed";
     return bail(FOAP4_E_HIP);
   }
-  m->cap_blocks = cap;
   // set-up of the allocation-free totals on this device (once per device)
   if (hipGetDevice(&m->device) != hipSuccess || noalloc_scratch_init(m->device) != hipSuccess ||
       hipDeviceGetAttribute(&m->n_cu, hipDeviceAttributeMultiprocessorCount, m->device) != hipSuccess || m->n_cu < 1) {
@@ -353,7 +353,7 @@ foap4_status foap4_mesh_create(const foap4_mesh_desc *desc, void *state0, void *
 foap4_status foap4_mesh_destroy(foap4_mesh *m) {
   if (!m) return FOAP4_OK;
   if (m->stream) (void)hipStreamSynchronize(m->stream);
-  void *ptrs[] = {m->d_level, m->d_gc, m->d_keys, m->d_scal, m->d_dev, m->d_item_begin,
+  void *ptrs[] = {m->d_leaf, m->d_map, m->d_scal, m->d_dev,
                   m->pat.srl, m->pat.f2c, m->pat.c2f, m->pat.bc, m->pat.face_info, m->pat.fix_list,
                   m->pat.cnt, m->pat.tot, m->pat.bflux_f, m->pat.bflux_c, m->pat.srl_c2f, m->d_ind, m->d_featcap};
   for (void *p : ptrs)
@@ -737,21 +737,25 @@ foap4_status foap4_regrid(foap4_mesh *m, const int8_t *flags_host, int32_t *chan
   std::vector<int32_t> op, src, arg;
   if (!m->topo.regrid(fl.data(), m->d.min_level, m->d.max_level, nl, op, src, arg)) return FOAP4_OK;
   if ((int64_t)nl.size() > m->d.max_blocks) return fail(m, FOAP4_E_CAPACITY, "regrid would exceed max_blocks");
-  // old ghosts feed the prolongation stencils
-  if ((st = fill(m, m->d_dev, 0)) != FOAP4_OK) return st;
-  std::vector<int32_t> map(3 * nl.size());
+  // old ghosts feed the prolongation stencils (coarsening and copies read none)
+  if (std::find(op.begin(), op.end(), 1) != op.end() && (st = fill(m, m->d_dev, 0)) != FOAP4_OK) return st;
+  m->h_map.resize(3 * nl.size());
   for (size_t i = 0; i < nl.size(); i++) {
-    map[3 * i] = op[i];
-    map[3 * i + 1] = src[i];
-    map[3 * i + 2] = arg[i];
+    m->h_map[3 * i] = op[i];
+    m->h_map[3 * i + 1] = src[i];
+    m->h_map[3 * i + 2] = arg[i];
   }
-  int32_t *d_map = nullptr;
-  F4_HIP(m, hipMalloc((void **)&d_map, map.size() * 4 + 4));
-  hipError_t e = hipMemcpyAsync(d_map, map.data(), map.size() * 4, hipMemcpyHostToDevice, m->stream);
-  if (e == hipSuccess) e = launch_remap(m, m->state[m->cur], m->state[1 - m->cur], d_map, (int64_t)nl.size(), m->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
-  (void)hipFree(d_map);
-  if (e != hipSuccess) return fail(m, FOAP4_E_HIP, std::string("remap: ") + hipGetErrorString(e));
+  const size_t map_bytes = m->h_map.size() * 4;
+  if (m->cap_map < map_bytes) {
+    if (m->d_map) F4_HIP(m, hipFree(m->d_map));
+    m->d_map = nullptr;
+    m->cap_map = 0;
+    F4_HIP(m, hipMalloc((void **)&m->d_map, map_bytes));
+    m->cap_map = map_bytes;
+  }
+  // not waited for: the pattern build below synchronizes
+  F4_HIP(m, hipMemcpyAsync(m->d_map, m->h_map.data(), map_bytes, hipMemcpyHostToDevice, m->stream));
+  F4_HIP(m, launch_remap(m, m->state[m->cur], m->state[1 - m->cur], m->d_map, (int64_t)nl.size(), m->stream));
   m->cur = 1 - m->cur;
   m->topo.leaves.swap(nl);
   m->topo.sort_and_index();

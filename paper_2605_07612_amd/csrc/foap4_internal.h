@@ -6,7 +6,6 @@
 #include <array>
 #include <cstdint>
 #include <string>
-#include <unordered_map>
 #include <vector>
 
 #include "foap4.h"
@@ -49,12 +48,36 @@ struct Leaf {
   int32_t g[3];  // global integer coordinates at `level` (tree * 2^level + anchor)
 };
 
-struct LeafHash {
-  size_t operator()(const std::array<int32_t, 4> &k) const {
-    uint64_t h = 1469598103934665603ull;
-    for (int32_t v : k) { h ^= (uint32_t)v; h *= 1099511628211ull; }
-    return (size_t)h;
+// Leaf index by (level, coordinates): open addressing over packed 64-bit keys.
+class LeafIndex {
+ public:
+  void reset(size_t n) {
+    size_t cap = 16;
+    while (cap < 2 * n) cap *= 2;
+    key_.assign(cap, kEmpty);
+    val_.resize(cap);
   }
+  void insert(uint64_t key, int32_t v) {  // at most the n of reset()
+    size_t i = slot(key);
+    while (key_[i] != kEmpty) i = (i + 1) & (key_.size() - 1);
+    key_[i] = key;
+    val_[i] = v;
+  }
+  int32_t find(uint64_t key) const {
+    if (key_.empty()) return -1;
+    for (size_t i = slot(key); key_[i] != kEmpty; i = (i + 1) & (key_.size() - 1))
+      if (key_[i] == key) return val_[i];
+    return -1;
+  }
+
+ private:
+  static constexpr uint64_t kEmpty = ~0ull;
+  size_t slot(uint64_t key) const {
+    uint64_t h = key * 0x9E3779B97F4A7C15ull;  // 2^64 / golden ratio
+    return (size_t)(h ^ h >> 32) & (key_.size() - 1);
+  }
+  std::vector<uint64_t> key_;
+  std::vector<int32_t> val_;
 };
 
 // Host-side forest of trees: leaf table, lookup, regrid (refine, 2:1 corner
@@ -78,7 +101,8 @@ class Topology {
               std::vector<int32_t> &op, std::vector<int32_t> &src, std::vector<int32_t> &arg) const;
 
  private:
-  std::unordered_map<std::array<int32_t, 4>, int64_t, LeafHash> index_;
+  uint64_t pack(int32_t level, const int32_t g[3]) const;
+  LeafIndex index_;
 };
 
 // Device descriptor of one mesh as the kernels see it (copied to the device).
@@ -166,16 +190,21 @@ struct foap4_mesh {
   int32_t cur = 0;
   f4::Topology topo;
   int64_t revision = 0;
-  // device copies of the leaf table
+  // device copy of the leaf table: keys, levels, coordinates in one array of
+  // max_blocks leaves, and what was last sent
+  void *d_leaf = nullptr;
   int32_t *d_level = nullptr, *d_gc = nullptr;
   uint64_t *d_keys = nullptr;
-  size_t cap_blocks = 0;
+  std::vector<uint8_t> h_leaf;
+  // remap list of the last regrid (grows as needed)
+  int32_t *d_map = nullptr;
+  size_t cap_map = 0;
+  std::vector<int32_t> h_map;
   f4::Pattern pat;
   bool pat_valid = false;
   double *d_scal = nullptr;
   bool dt_valid = false;
   f4::MeshDev *d_dev = nullptr;  // two descriptors of this mesh: stored ghosts, and the steps' (gathered halos)
-  int64_t *d_item_begin = nullptr;
   // refinement indicator: default for regrid, attached MLP, scratch
   foap4_indicator ind = FOAP4_IND_LOHNER;
   const foap4_mlp *mlp = nullptr;
