@@ -141,8 +141,7 @@ foap4_status upload_dev(foap4_mesh *m) {
 }
 
 // Copies the leaf table to the device: keys, levels and coordinates in one
-// array and one copy.  Not waited for (h_leaf stays): the pattern build, which
-// follows every upload, synchronizes.
+// array and one copy.
 static foap4_status upload_leaves(foap4_mesh *m) {
   const size_t nb = m->topo.leaves.size();
   m->h_leaf.resize(24 * nb);
@@ -158,6 +157,7 @@ static foap4_status upload_leaves(foap4_mesh *m) {
   m->d_level = (int32_t *)(m->d_keys + nb);
   m->d_gc = m->d_level + nb;
   if (nb) F4_HIP(m, hipMemcpyAsync(m->d_leaf, m->h_leaf.data(), 24 * nb, hipMemcpyHostToDevice, m->stream));
+  F4_HIP(m, hipStreamSynchronize(m->stream));
   return FOAP4_OK;
 }
 

@@ -238,6 +238,7 @@ struct MlpResult {
 // BF16 MFMA operand fragments and the gradient workspace, all on the device.
 struct foap4_mlp {
   hipStream_t stream = nullptr;
+  void *d_fixed = nullptr;     // the allocation that holds what has a fixed size:
   float *d_w = nullptr;        // [kMlpParams] flat W1 b1 W2 b2 W3 b3
   double *d_mv = nullptr;      // [2][kMlpParams] Adam first and second moments
   f4::MlpResult *d_res = nullptr, *h_res = nullptr;  // last evaluation, on the device and in pinned host memory

@@ -790,18 +790,28 @@ foap4_status foap4_mlp_create(void *hip_stream, foap4_mlp **out) {
   *out = nullptr;
   foap4_mlp *net = new foap4_mlp();
   net->stream = (hipStream_t)hip_stream;
-  if (hipMalloc((void **)&net->d_w, kMlpParams * 4) != hipSuccess ||
-      hipMalloc((void **)&net->d_mv, 2 * kMlpParams * 8) != hipSuccess ||
-      hipMalloc((void **)&net->d_res, sizeof(MlpResult)) != hipSuccess ||
-      hipHostMalloc((void **)&net->h_res, sizeof(MlpResult)) != hipSuccess ||
-      hipMalloc(&net->d_frag, kMlpFrags * 64 * 16) != hipSuccess ||
-      hipMalloc((void **)&net->d_cls, 4 * 4) != hipSuccess ||
-      hipMalloc((void **)&net->d_ticket, 4) != hipSuccess ||
-      hipMemsetAsync(net->d_ticket, 0, 4, net->stream) != hipSuccess ||
-      hipMalloc((void **)&net->d_cnt, kCountGrid * 4 * 8) != hipSuccess) {
+  // one allocation for everything of fixed size, each part 256-byte aligned
+  size_t bytes = 0;
+  auto part = [&](size_t n) {
+    const size_t at = bytes;
+    bytes += (n + 255) & ~(size_t)255;
+    return at;
+  };
+  const size_t w = part(kMlpParams * 4), mv = part(2 * kMlpParams * 8), res = part(sizeof(MlpResult)),
+               frag = part(kMlpFrags * 64 * 16), cls = part(4 * 4), cnt = part(kCountGrid * 4 * 8), ticket = part(4);
+  char *p = nullptr;
+  if (hipMalloc(&net->d_fixed, bytes) != hipSuccess ||
+      hipMemsetAsync((p = (char *)net->d_fixed) + ticket, 0, 4, net->stream) != hipSuccess) {
     foap4_mlp_destroy(net);
     return mlp_fail(nullptr, FOAP4_E_HIP, "device allocation failed");
   }
+  net->d_w = (float *)(p + w);
+  net->d_mv = (double *)(p + mv);
+  net->d_res = (MlpResult *)(p + res);
+  net->d_frag = p + frag;
+  net->d_cls = (float *)(p + cls);
+  net->d_cnt = (unsigned long long *)(p + cnt);
+  net->d_ticket = (unsigned *)(p + ticket);
   *out = net;
   return FOAP4_OK;
 }
@@ -809,8 +819,7 @@ foap4_status foap4_mlp_create(void *hip_stream, foap4_mlp **out) {
 foap4_status foap4_mlp_destroy(foap4_mlp *net) {
   if (!net) return FOAP4_OK;
   (void)hipStreamSynchronize(net->stream);
-  void *ptrs[] = {net->d_w, net->d_mv, net->d_res, net->d_frag, net->d_cls, net->d_cnt, net->d_ticket, net->d_part,
-                  net->d_loss};
+  void *ptrs[] = {net->d_fixed, net->d_part, net->d_loss};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   if (net->h_res) (void)hipHostFree(net->h_res);
@@ -889,7 +898,9 @@ static foap4_status check_counts(foap4_mlp *net, const unsigned long long *cnt, 
   return FOAP4_OK;
 }
 
+// what only training needs: the partial gradients and the pinned results
 static foap4_status ensure_part(foap4_mlp *net, size_t groups) {
+  if (!net->h_res) M_HIP(net, hipHostMalloc((void **)&net->h_res, sizeof(MlpResult)));
   if (net->cap_part >= groups) return FOAP4_OK;
   if (net->d_part) M_HIP(net, hipFree(net->d_part));
   net->d_part = nullptr;
