@@ -89,21 +89,23 @@ __device__ __forceinline__ void pin(T &a) {
 // LP = 24 values apart: 24 = -8 mod 32 banks, so the half waves of an 8 x 8
 // tile (four adjacent rows) and of a 16 x 16 tile (rows r and r + 2, see the
 // lane map) touch every bank once.
-template <int TS>
+template <typename T, int TS>
 struct WenoTile {
-  static constexpr int LP = 24, Q = TS + 6;   // plane rows -3 .. TS + 2, row stride LP
+  static constexpr int Q = TS + 6;                           // plane rows -3 .. TS + 2
+  static constexpr int LP = sizeof(T) == 4 ? 24 : Q;         // their stride
   static constexpr int PLANE = Q * LP;
-  static constexpr int FACES = (TS + 1) * LP;  // face values: rows of LP
+  static constexpr int LF = sizeof(T) == 4 ? 24 : TS + 1;    // row stride of the face values
+  static constexpr int FACES = (TS + 1) * LF;
   static constexpr int RING = (12 * TS + TS * TS - 1) / (TS * TS);  // halo cells per thread
 };
 
 template <typename T, int NDIM, int TS, int SCH, int STG>
 __global__ __launch_bounds__(TS *TS) void weno_kernel(const MeshDev *__restrict__ Mp, int64_t total, int kd, SubStep ss) {
-  using C = WenoTile<TS>;
-  constexpr int NV = NDIM + 2, NF = 2 * NDIM, LP = C::LP, PLANE = C::PLANE, RING = C::RING;
+  using C = WenoTile<T, TS>;
+  constexpr int NV = NDIM + 2, NF = 2 * NDIM, LP = C::LP, LF = C::LF, PLANE = C::PLANE, RING = C::RING;
   __shared__ T Ws[NV * PLANE];     // primitives: cell (x, y) at (y + 3) LP + x + 3
-  __shared__ T Fx[NV * C::FACES];  // face x - 1/2 of row y at y LP + x: left value, then flux
-  __shared__ T Fy[NV * C::FACES];  // face y - 1/2 of column x at y LP + x
+  __shared__ T Fx[NV * C::FACES];  // face x - 1/2 of row y at y LF + x: left value, then flux
+  __shared__ T Fy[NV * C::FACES];  // face y - 1/2 of column x at y LF + x
   const MeshDev &M = *Mp;
   // XCD-aware tile order: XCD x = w mod 8 takes the contiguous tiles
   // [x q + min(x, r), ...), total = 8 q + r
@@ -305,10 +307,10 @@ __global__ __launch_bounds__(TS *TS) void weno_kernel(const MeshDev *__restrict_
         T hi;
         weno5(c[-2], c[-1], c[0], c[1], c[2], xl[v], hi);
         pin(xl[v], hi);
-        Fx[v * C::FACES + tj * LP + ti + 1] = hi;
+        Fx[v * C::FACES + tj * LF + ti + 1] = hi;
         weno5(c[-2 * LP], c[-LP], c[0], c[LP], c[2 * LP], yl[v], hi);
         pin(yl[v], hi);
-        Fy[v * C::FACES + (tj + 1) * LP + ti] = hi;
+        Fy[v * C::FACES + (tj + 1) * LF + ti] = hi;
       }
     }
     // The halo cells next to the tile: 4 TS one-sided reconstructions, one
@@ -331,7 +333,7 @@ __global__ __launch_bounds__(TS *TS) void weno_kernel(const MeshDev *__restrict_
         pin(E[v]);
       }
       if (!eup) {
-        T *d = ey ? Fy + em : Fx + em * LP;
+        T *d = ey ? Fy + em : Fx + em * LF;
 #pragma unroll
         for (int v = 0; v < NV; v++) d[v * C::FACES] = E[v];
       }
@@ -364,14 +366,14 @@ __global__ __launch_bounds__(TS *TS) void weno_kernel(const MeshDev *__restrict_
     // thread that evaluates it
     {
       T L[NV], F[NV];
-      T *f = Fx + tj * LP + ti;
+      T *f = Fx + tj * LF + ti;
 #pragma unroll
       for (int v = 0; v < NV; v++) L[v] = f[v * C::FACES];
       riemann<T, NDIM, 0, (SCH & kSchHLL) != 0>(L, xl, gamma, F);
 #pragma unroll
       for (int v = 0; v < NV; v++) f[v * C::FACES] = F[v];
       if (I == 0) bflux(0, J, k, F);
-      f = Fy + tj * LP + ti;
+      f = Fy + tj * LF + ti;
 #pragma unroll
       for (int v = 0; v < NV; v++) L[v] = f[v * C::FACES];
       riemann<T, NDIM, 1, (SCH & kSchHLL) != 0>(L, yl, gamma, F);
@@ -382,7 +384,7 @@ __global__ __launch_bounds__(TS *TS) void weno_kernel(const MeshDev *__restrict_
     if (extra && eup) {
       // y faces on exchanged velocities, so that both sides' lanes evaluate
       // an x-normal flux
-      T *f = ey ? Fy + TS * LP + em : Fx + em * LP + TS;
+      T *f = ey ? Fy + TS * LF + em : Fx + em * LF + TS;
       T L[NV], R[NV], F[NV];
 #pragma unroll
       for (int v = 0; v < NV; v++) L[v] = f[v * C::FACES];
@@ -423,8 +425,8 @@ __global__ __launch_bounds__(TS *TS) void weno_kernel(const MeshDev *__restrict_
     const auto ro = buf_rsrc(uo + k * sk);
 #pragma unroll
     for (int v = 0; v < NV; v++) {
-      const T *fx = Fx + v * C::FACES + tj * LP + ti, *fy = Fy + v * C::FACES + tj * LP + ti;
-      T div = (fx[1] - fx[0]) + (fy[LP] - fy[0]);
+      const T *fx = Fx + v * C::FACES + tj * LF + ti, *fy = Fy + v * C::FACES + tj * LF + ti;
+      T div = (fx[1] - fx[0]) + (fy[LF] - fy[0]);
       if constexpr (NDIM == 3) {
         div += Fz1[v] - Fz[v];
         Fz[v] = Fz1[v];
