@@ -48,7 +48,7 @@ def build(verbose: bool = True) -> str:
     units = [u for u in UNITS if os.path.exists(os.path.join(CSRC, u[0]))]
     jobs = min(len(units), max(1, min(8, os.cpu_count() or 1)))
     # longest compiles first
-    units.sort(key=lambda u: u[0] != "stage.hip" and u[0] != "mlp.hip")
+    units.sort(key=lambda u: u[0] not in ("stage.hip", "advect.hip", "mlp.hip"))
     with cf.ThreadPoolExecutor(jobs) as ex:
         objs = list(ex.map(_compile, units))
     tmp = OUT + f".tmp{os.getpid()}"

@@ -2,10 +2,10 @@
 // carried by a uniform velocity v, rho_t + div(rho v) = 0.  The face values
 // come from the mesh's reconstruction (minmod or van Leer MUSCL, WENO5), the
 // physical flux on either side of a face is rho v_d, and the numerical flux
-// (Rusanov or HLL) takes the wave speeds min(v_d, 0) and max(v_d, 0).
+// (Rusanov or HLL with the wave speeds min(v_d, 0) and max(v_d, 0)) is upwind.
 //
-// One workgroup per block and one thread per (i, j) column, which marches
-// along k.  Per plane the workgroup stages the plane with its x and y face
+// One workgroup per block, or per slab of its planes where the blocks do not
+// fill the chip, and one thread per (i, j) column, which marches along k.  Per plane the workgroup stages the plane with its x and y face
 // halos in LDS (the interior from the threads' own z windows; the halo of a
 // same-level face straight from the neighbouring block's interior when the
 // mesh gathers halos, else - and always across refinement and boundary
@@ -16,9 +16,12 @@
 // upper face of the previous plane).  The update, the refinement-face flux
 // capture and the CFL epilogue follow the Euler stage kernels: stage 1 / 2
 // Heun's stages, 3 the generic sub-step, 4 the generic sub-step with three
-// earlier states.  With a single variable the work per cell is small, so the
-// kernel is bound by its HBM traffic: the state is read once per stage (plus
-// the face halos, and Heun's second stage reads U^n) and written once.
+// earlier states.  A stage moves the state once in and once out (Heun's second
+// also reads U^n), 61 us for two steps of 256^3 cells in FP32 at the rate of a
+// large copy; the kernel takes 205 us there (227 with two reconstructions per
+// face), bound by its VALU work on the faces, the LDS rows and the addresses.
+// FP64 plain 335 us, WENO5 FP64 899 us (729 and 1985 with two reconstructions,
+// whole blocks and halos from a ghost-fill pass).
 #include <type_traits>
 
 #include "device_common.h"
@@ -55,25 +58,24 @@ __device__ __forceinline__ T adv_weno5(T v0, T v1, T v2, T v3, T v4) {
   return fdiv(a0 * q0 + a1 * q1 + a2 * q2, a0 + a1 + a2);
 }
 
-// Numerical flux through the face between cells w[R-1] and w[R] of the 2R
-// cells w[0 .. 2R-1] along the face normal, velocity component v.
-// Rusanov: (v L + v R)/2 - |v| (R - L)/2 (the largest of |min(v, 0)| and
-// |max(v, 0)| is |v|).  HLL with s0 = min(v, 0), s1 = max(v, 0): the left
-// flux v L when s0 >= 0, else (s1 = 0) the right flux v R.
-template <typename T, int LIM, bool HLL>
-__device__ __forceinline__ T adv_flux(const T *w, T v) {
-  T L, R;
-  if constexpr (LIM == 2) {
-    L = adv_weno5(w[0], w[1], w[2], w[3], w[4]);
-    R = adv_weno5(w[5], w[4], w[3], w[2], w[1]);
-  } else {
-    const T s1 = limit<LIM>(w[1] - w[0], w[2] - w[1]);
-    const T s2 = limit<LIM>(w[2] - w[1], w[3] - w[2]);
-    L = w[1] + T(0.5) * s1;
-    R = w[2] - T(0.5) * s2;
-  }
-  if constexpr (HLL) return v >= T(0) ? L * v : R * v;
-  else return T(0.5) * (L * v + R * v) - T(0.5) * fabs(v) * (R - L);
+// Value of cell `at` (relative) at its face in direction DIR (+1: upper), get(k)
+// the cell k cells above.
+template <typename T, int LIM, int DIR, typename Get>
+__device__ __forceinline__ T adv_value(Get get, int at) {
+  const T b = get(at - DIR), c = get(at), d = get(at + DIR);
+  if constexpr (LIM == 2) return adv_weno5(T(get(at - 2 * DIR)), b, c, d, T(get(at + 2 * DIR)));
+  else return c + T(0.5) * limit<LIM>(c - b, d - c);
+}
+
+// Numerical flux through the upper face of cell 0, velocity component v (the
+// same on the whole mesh), get(k) the cell k cells above.  Rusanov's flux
+// (v L + v R)/2 - |v| (R - L)/2 (the largest of |min(v, 0)| and |max(v, 0)| is
+// |v|) and HLL with s0 = min(v, 0), s1 = max(v, 0) are both the upwind flux,
+// v L for v >= 0 and v R below: one reconstruction per face, not two.  (A NaN
+// or infinite cell then reaches only its downwind neighbours.)
+template <typename T, int LIM, typename Get>
+__device__ __forceinline__ T adv_flux(Get get, T v) {
+  return v * (v >= T(0) ? adv_value<T, LIM, 1>(get, 0) : adv_value<T, LIM, -1>(get, 1));
 }
 
 // Stores the refinement-face flux F of face f at in-face position (t1, t2)
@@ -95,23 +97,27 @@ __host__ __device__ constexpr int adv_lds(int N, int g) { return 2 * (N + 2 * g)
 // for 32^2 columns, 256 for 8^2 and 16^2 (which leaves the compiler up to 512
 // registers per thread instead of 128).  HS: halo cells per thread and
 // plane, ceil(4 g N / N^2): 1, or 2 for 8^2 columns with g >= 3 (N >= 2 g
-// bounds it by 2).  Every register saved is worth it here: the kernel waits
-// on its loads, and more waves per SIMD hide more of that.
-template <typename T, int NDIM, int LIM, bool HLL, int STG, int MAXT, int HS>
-__global__ __launch_bounds__(MAXT) void advect_kernel(const MeshDev *__restrict__ Mp, SubStep ss) {
+// bounds it by 2).  Eight waves per SIMD asked of the compiler for FP32 MUSCL
+// gained 10 % on 8^3 blocks and lost 4 % on 256^3 cells (205 -> 213 us).
+template <typename T, int NDIM, int LIM, int STG, int MAXT, int HS, bool SLABS>
+__global__ __launch_bounds__(MAXT) void advect_kernel(const MeshDev *__restrict__ Mp, int lslabs, SubStep ss) {
   constexpr int R = AdvStencil<LIM>::R;
   extern __shared__ __align__(16) unsigned char adv_smem[];
   const MeshDev &M = *Mp;
   const int N = M.N, g = M.g, P = N + 2 * g, Q = P;
   const int rows = (NDIM == 3) ? P * P : P;  // rows (k, j) of the row part of a block
   const int64_t sv = (NDIM == 3) ? (int64_t)P * P * P : (int64_t)P * P;
-  // XCD-aware block order: workgroup w runs on XCD w mod 8, so XCD x is
-  // given the contiguous range of blocks [x q + min(x, r), ...) of q or q + 1
-  // blocks (nb = 8 q + r): blocks that are neighbours in Morton order, whose
-  // face halos each reads, share that XCD's L2.  A bijection onto 0 .. nb-1.
-  const int64_t nbk = M.nb, xq = nbk / 8, xr = nbk % 8;
+  // XCD-aware order: workgroup w runs on XCD w mod 8, so XCD x is given the
+  // contiguous range of (block, slab) items [x q + min(x, r), ...) of q or q + 1
+  // items (8 q + r in all): blocks that are neighbours in Morton order, whose
+  // face halos each reads, share that XCD's L2.  A bijection onto all items.
+  const int64_t all = SLABS ? M.nb << lslabs : M.nb, xq = all / 8, xr = all % 8;
   const int64_t xid = blockIdx.x % 8, xi = blockIdx.x / 8;
-  const int64_t b = xid * xq + (xid < xr ? xid : xr) + xi;
+  const int64_t item = xid * xq + (xid < xr ? xid : xr) + xi;
+  // slabs of N >> lslabs planes per block
+  const int64_t b = SLABS ? item >> lslabs : item;
+  const int kd = SLABS ? N >> lslabs : (NDIM == 3) ? N : 1;
+  const int k0 = SLABS ? (int)(item & ((1 << lslabs) - 1)) * kd : 0, k1 = k0 + kd;
   const int t = threadIdx.x, i = t % N, j = t / N;
   const int cur = M.cur;
   const int64_t boff = b * sv;
@@ -241,18 +247,27 @@ __global__ __launch_bounds__(MAXT) void advect_kernel(const MeshDev *__restrict_
   T w[2 * R];
   if constexpr (NDIM == 3) {
 #pragma unroll
-    for (int s = 1; s < 2 * R; s++) w[s] = cell(i, j, s - R);
+    for (int s = 1; s < 2 * R; s++) w[s] = cell(i, j, k0 + s - R);
   }
-  const int nk = (NDIM == 3) ? N : 1;
-  fetch(0, I0{});
+  fetch(k0, I0{});
   if constexpr (D > 1) {
-    if (1 < nk) fetch(1, I1{});
+    if (k0 + 1 < k1) fetch(k0 + 1, I1{});
   }
   if constexpr (D > 2) {
-    if (2 < nk) fetch(2, I2{});
-    if (3 < nk) fetch(3, I3{});
+    if (k0 + 2 < k1) fetch(k0 + 2, I2{});
+    if (k0 + 3 < k1) fetch(k0 + 3, I3{});
   }
   T Fz = T(0);  // flux through the lower z face of the current plane
+  // fluxes through a cell's lower and upper face (one test of the sign)
+  auto pair = [&](auto get, T v, T &fm, T &fp) __attribute__((always_inline)) {
+    if (v >= T(0)) {
+      fm = v * adv_value<T, LIM, 1>(get, -1);
+      fp = v * adv_value<T, LIM, 1>(get, 0);
+    } else {
+      fm = v * adv_value<T, LIM, -1>(get, 0);
+      fp = v * adv_value<T, LIM, -1>(get, 1);
+    }
+  };
   auto plane = [&](const int k, auto slot) __attribute__((always_inline)) {
     constexpr int S = decltype(slot)::value;
     T *pl = lds + (k & 1) * Q * Q;  // cell (x, y) at (y + g) Q + x + g
@@ -271,33 +286,29 @@ __global__ __launch_bounds__(MAXT) void advect_kernel(const MeshDev *__restrict_
       if (hv[q]) pl[(hy[q] + g) * Q + hx[q] + g] = hq[S][q];
     const T cp = (STG >= 2) ? pq[S] : T(0);
     const T cp2 = (STG == 4) ? pq2[S] : T(0), cp3 = (STG == 4) ? pq3[S] : T(0);
-    if (k + D < nk) fetch(k + D, slot);
+    if (k + D < k1) fetch(k + D, slot);
     __syncthreads();
     // x faces i - 1/2 and i + 1/2, then y faces, from the staged plane
-    T sx[2 * R + 1], sy[2 * R + 1];
-#pragma unroll
-    for (int s = 0; s < 2 * R + 1; s++) {
-      sx[s] = pl[(j + g) * Q + i + g + s - R];
-      sy[s] = pl[(j + g + s - R) * Q + i + g];
-    }
-    const T fxm = adv_flux<T, LIM, HLL>(sx, vx), fxp = adv_flux<T, LIM, HLL>(sx + 1, vx);
+    const T *own = pl + (j + g) * Q + i + g;
+    T fxm, fxp, fym, fyp;
+    pair([&](int s) { return s == 0 ? c : own[s]; }, vx, fxm, fxp);
     T div = fxp - fxm;
     if (i == 0) adv_bflux<T, NDIM>(M, finfo[0], j, k, fxm);
     if (i == N - 1) adv_bflux<T, NDIM>(M, finfo[1], j, k, fxp);
-    const T fym = adv_flux<T, LIM, HLL>(sy, vy), fyp = adv_flux<T, LIM, HLL>(sy + 1, vy);
+    pair([&](int s) { return s == 0 ? c : own[s * Q]; }, vy, fym, fyp);
     div += fyp - fym;
     if (j == 0) adv_bflux<T, NDIM>(M, finfo[2], i, k, fym);
     if (j == N - 1) adv_bflux<T, NDIM>(M, finfo[3], i, k, fyp);
     if constexpr (NDIM == 3) {
-      if (k == 0) {  // the block's lower z face, from cells -R .. R-1
+      if (k == k0) {  // the slab's lower z face, from cells k0 - R .. k0 + R - 1
         T w0[2 * R];
-        w0[0] = cell(i, j, -R);
+        w0[0] = cell(i, j, k0 - R);
 #pragma unroll
         for (int s = 1; s < 2 * R; s++) w0[s] = w[s - 1];
-        Fz = adv_flux<T, LIM, HLL>(w0, vz);
-        adv_bflux<T, NDIM>(M, finfo[4], i, j, Fz);
+        Fz = adv_flux<T, LIM>([&](int s) { return w0[s + R - 1]; }, vz);
+        if (k0 == 0) adv_bflux<T, NDIM>(M, finfo[4], i, j, Fz);
       }
-      const T fzp = adv_flux<T, LIM, HLL>(w, vz);
+      const T fzp = adv_flux<T, LIM>([&](int s) { return w[s + R - 1]; }, vz);
       div += fzp - Fz;
       if (k == N - 1) adv_bflux<T, NDIM>(M, finfo[5], i, j, fzp);
       Fz = fzp;
@@ -316,16 +327,16 @@ __global__ __launch_bounds__(MAXT) void advect_kernel(const MeshDev *__restrict_
       if (!isfinite(out)) atomic_max_pos(&M.scal[kBad], 1.0);
     }
   };
-  for (int k = 0; k < nk; k += D) {
+  for (int k = k0; k < k1; k += D) {
     plane(k, I0{});
     if constexpr (D > 1) {
-      if (k + 1 >= nk) break;
+      if (k + 1 >= k1) break;
       plane(k + 1, I1{});
     }
     if constexpr (D > 2) {
-      if (k + 2 >= nk) break;
+      if (k + 2 >= k1) break;
       plane(k + 2, I2{});
-      if (k + 3 >= nk) break;
+      if (k + 3 >= k1) break;
       plane(k + 3, I3{});
     }
   }
@@ -337,11 +348,30 @@ __global__ __launch_bounds__(MAXT) void advect_kernel(const MeshDev *__restrict_
   }
 }
 
-template <typename T, int NDIM, int LIM, bool HLL>
-static void launch_adv(unsigned nb, int N, int g, const MeshDev *d, int stage, const SubStep &ss, hipStream_t s) {
+template <typename T, int NDIM, int LIM>
+static void launch_adv(int64_t nb, int N, int g, const MeshDev *d, int stage, const SubStep &ss, hipStream_t s) {
   const unsigned threads = (unsigned)(N * N);
+  // A block per workgroup, or slabs of its planes (halved as long as needed)
+  // where whole blocks leave CUs without waves to hide their loads behind: up to
+  // two workgroups of 256 threads a CU, one of 64.  Two Heun steps, van Leer, us:
+  // FP32 180 blocks of 16^3 61 whole, 48; 27 of 32^3 132 and 46; 80 of 32^3 135
+  // and 86 (100 with twice as many); one of 32^3 124 and 29; 512 of 8^3 49 and
+  // 59; FP64 WENO5 80 of 32^3 462 and 248.  Its own variant, because the slab's
+  // bounds cost registers that whole blocks need (256^3 cells: 197 and 214).
+  int ls = 0;
+  if (NDIM == 3) {
+    const int64_t want = N == 8 ? 256 * 64 : 512 * 256;
+    while ((N >> ls) > 1 && ((nb * threads) << ls) < want) ls++;
+  }
+  const unsigned grid = (unsigned)(nb << ls);
   const size_t lds = (size_t)adv_lds(N, g) * sizeof(T);
-#define F4_ADV(STG, MAXT, HS) advect_kernel<T, NDIM, LIM, HLL, STG, MAXT, HS><<<nb, threads, lds, s>>>(d, ss)
+#define F4_ADV(STG, MAXT, HS)                                                                                 \
+  do {                                                                                                       \
+    if (NDIM == 3 && ls > 0)                                                                                 \
+      advect_kernel<T, NDIM, LIM, STG, MAXT, HS, NDIM == 3><<<grid, threads, lds, s>>>(d, ls, ss);           \
+    else                                                                                                     \
+      advect_kernel<T, NDIM, LIM, STG, MAXT, HS, false><<<grid, threads, lds, s>>>(d, 0, ss);                \
+  } while (0)
 #define F4_ADV_STAGES(MAXT, HS)                \
   switch (stage) {                             \
     case 1: F4_ADV(1, MAXT, HS); break;        \
@@ -363,30 +393,23 @@ static void launch_adv(unsigned nb, int N, int g, const MeshDev *d, int stage, c
 }
 
 template <typename T, int NDIM>
-static void launch_adv_scheme(unsigned nb, int N, int g, const MeshDev *d, int stage, int limiter, bool hll,
-                              const SubStep &ss, hipStream_t s) {
-  if (limiter == FOAP4_LIM_WENO5) {
-    if (hll) launch_adv<T, NDIM, 2, true>(nb, N, g, d, stage, ss, s);
-    else launch_adv<T, NDIM, 2, false>(nb, N, g, d, stage, ss, s);
-  } else if (limiter == FOAP4_LIM_VANLEER) {
-    if (hll) launch_adv<T, NDIM, 1, true>(nb, N, g, d, stage, ss, s);
-    else launch_adv<T, NDIM, 1, false>(nb, N, g, d, stage, ss, s);
-  } else {
-    if (hll) launch_adv<T, NDIM, 0, true>(nb, N, g, d, stage, ss, s);
-    else launch_adv<T, NDIM, 0, false>(nb, N, g, d, stage, ss, s);
-  }
+static void launch_adv_limiter(int64_t nb, int N, int g, const MeshDev *d, int stage, int limiter, const SubStep &ss,
+                               hipStream_t s) {
+  if (limiter == FOAP4_LIM_WENO5) launch_adv<T, NDIM, 2>(nb, N, g, d, stage, ss, s);
+  else if (limiter == FOAP4_LIM_VANLEER) launch_adv<T, NDIM, 1>(nb, N, g, d, stage, ss, s);
+  else launch_adv<T, NDIM, 0>(nb, N, g, d, stage, ss, s);
 }
 
 hipError_t launch_advect_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int n_ghost, int stage, int ndim,
-                               bool f64, int limiter, bool hll, hipStream_t s, const SubStep &ss) {
+                               bool f64, int limiter, hipStream_t s, const SubStep &ss) {
   if (nblocks <= 0) return hipSuccess;
-  const unsigned nb = (unsigned)nblocks;
+  const int64_t nb = nblocks;
   if (f64) {
-    if (ndim == 3) launch_adv_scheme<double, 3>(nb, block_n, n_ghost, d_mesh, stage, limiter, hll, ss, s);
-    else launch_adv_scheme<double, 2>(nb, block_n, n_ghost, d_mesh, stage, limiter, hll, ss, s);
+    if (ndim == 3) launch_adv_limiter<double, 3>(nb, block_n, n_ghost, d_mesh, stage, limiter, ss, s);
+    else launch_adv_limiter<double, 2>(nb, block_n, n_ghost, d_mesh, stage, limiter, ss, s);
   } else {
-    if (ndim == 3) launch_adv_scheme<float, 3>(nb, block_n, n_ghost, d_mesh, stage, limiter, hll, ss, s);
-    else launch_adv_scheme<float, 2>(nb, block_n, n_ghost, d_mesh, stage, limiter, hll, ss, s);
+    if (ndim == 3) launch_adv_limiter<float, 3>(nb, block_n, n_ghost, d_mesh, stage, limiter, ss, s);
+    else launch_adv_limiter<float, 2>(nb, block_n, n_ghost, d_mesh, stage, limiter, ss, s);
   }
   return hipGetLastError();
 }

@@ -479,7 +479,7 @@ static hipError_t mesh_stage(foap4_mesh *m, int64_t items, int stage, const SubS
   const int ndim = m->d.ndim;
   if (m->d.physics == FOAP4_PHYS_ADVECTION)
     return launch_advect_stage(m->d_dev + 1, (int64_t)m->topo.leaves.size(), m->d.block_n, m->d.n_ghost, stage, ndim, f64,
-                               m->d.limiter, m->d.flux == FOAP4_FLUX_HLL, m->stream, ss);
+                               m->d.limiter, m->stream, ss);
   if (m->d.limiter == FOAP4_LIM_WENO5) {
     return launch_weno_stage(m->d_dev + 1, (int64_t)m->topo.leaves.size(), m->d.block_n, stage, ndim, f64, scheme_of(m->d),
                              m->stream, ss);
@@ -846,7 +846,7 @@ static hipError_t batch_stage(foap4_batch *b, int stage, int grid, hipStream_t s
     for (int i = 0; i < n; i++) {
       const foap4_mesh *m = b->meshes[i];
       hipError_t e = launch_advect_stage(b->d_devs + i, (int64_t)m->topo.leaves.size(), m->d.block_n, m->d.n_ghost,
-                                         stage, b->ndim, b->f64, m->d.limiter, m->d.flux == FOAP4_FLUX_HLL, s, ss);
+                                         stage, b->ndim, b->f64, m->d.limiter, s, ss);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;

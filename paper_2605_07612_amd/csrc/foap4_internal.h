@@ -300,9 +300,9 @@ hipError_t launch_stage(const MeshDev *d_meshes, int n_meshes, int64_t total_ite
 // weno.hip: the WENO5 stage (one workgroup per tile and k-slab)
 hipError_t launch_weno_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int stage, int ndim, bool f64,
                              int scheme, hipStream_t s, const SubStep &ss = SubStep{});
-// advect.hip: the scalar advection stage (one workgroup per block, stored ghosts)
+// advect.hip: the scalar advection stage (a workgroup per block or slab of planes)
 hipError_t launch_advect_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int n_ghost, int stage, int ndim,
-                               bool f64, int limiter, bool hll, hipStream_t s, const SubStep &ss = SubStep{});
+                               bool f64, int limiter, hipStream_t s, const SubStep &ss = SubStep{});
 // stage 1 of one mesh that also reduces the raw features of its input state
 // (feat_raw [nb][2], zeroed by the caller) by atomic maxima
 hipError_t launch_stage1_features(const MeshDev *d_mesh, int64_t total_items, int ndim, bool f64, int nmask,

@@ -89,6 +89,22 @@ def test_parity_uniform(f4, ndim, nt, N, limiter, flux, vel, prec):
 
 
 @pytest.mark.parametrize("prec", [1, 0], ids=["f64", "f32"])
+@pytest.mark.parametrize("nt,N,limiter,vel", [
+    (1, 8, "vanleer", (1.0, -1.0, 0.0)), (7, 8, "weno5", (-0.5, 0.4, -1.0)), (2, 16, "minmod", (0.0, 0.0, -1.0)),
+    (5, 16, "vanleer", (-1.0, -0.3, 0.7)), (8, 16, "weno5", (0.2, 1.0, 0.6)), (1, 32, "weno5", (0.0, -1.0, -1.0)),
+    (3, 32, "vanleer", (-0.4, 0.9, -0.6)), (5, 32, "minmod", (1.0, 0.0, 1.0)),
+])
+def test_parity_slabs(f4, nt, N, limiter, vel, prec):
+    """Meshes on both sides of the slab rule (slabs of one plane up to whole
+    blocks: 8^3 from 256 blocks, 16^3 from 512, 32^3 from 128), upwind from
+    either side and along no axis; two steps."""
+    gm, om = adv_pair(f4, 3, nt, N, prec, limiter, "rusanov", vel)
+    gm.step(2)
+    om.step(2)
+    compare(gm, om, prec, f"adv slabs nt={nt} N={N} {limiter} v={vel}")
+
+
+@pytest.mark.parametrize("prec", [1, 0], ids=["f64", "f32"])
 @pytest.mark.parametrize("integrator,limiter", [("ssprk3", "vanleer"), ("ssprk43", "minmod"), ("rk4", "weno5")])
 def test_parity_integrators(f4, integrator, limiter, prec):
     gm, om = adv_pair(f4, 3, 2, 16, prec, limiter, "rusanov", (1.0, -0.7, 0.5), integrator=integrator)
