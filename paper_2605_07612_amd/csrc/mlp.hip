@@ -300,8 +300,8 @@ struct WaveTiles {
   uint16_t d3[32 * 16];    // BF16 dz3, classes 3..15 zero
   float zf[32 * 4];        // logits
 };
-constexpr int kMlpSmem = (4 * (int)sizeof(WaveTiles) > (kMlpPartStride * 4)) ? 4 * (int)sizeof(WaveTiles)
-                                                                              : kMlpPartStride * 4;
+constexpr int kMlpSmem = (4 * (int)sizeof(WaveTiles) > (2 * kMlpPartStride * 4)) ? 4 * (int)sizeof(WaveTiles)
+                                                                                  : 2 * kMlpPartStride * 4;
 
 // Each wave takes chunks of 32 rows; the workgroup's four waves take four
 // consecutive chunks per round, and every wave of a workgroup runs the same
@@ -309,14 +309,27 @@ constexpr int kMlpSmem = (4 * (int)sizeof(WaveTiles) > (kMlpPartStride * 4)) ? 4
 // phases are uniform.  TRAIN: forward, softmax cross-entropy, backward with
 // the gradient accumulated in registers, then the workgroup's partial
 // gradient written to part[blockIdx.x] (waves summed in a fixed order).
+// Bound by latency: 64,510 rows are 504 workgroups of one chunk per wave, a
+// chain of loads, matrix products and LDS exchanges.  Two workgroups a CU run
+// them in one pass, which takes 256 registers or less: where z1 and z2 are
+// positive is kept as a bit each, not the values, and fragments and biases are
+// addressed by descriptors (a hoisted 64-bit address each took 70 registers).
+// One loss and gradient of 64,510 rows: 75 us at 364 registers and one
+// workgroup a CU, 59 now, 57 with the waves' sums added in two turns, not four.
 template <bool TRAIN>
-__global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
+__global__ __launch_bounds__(256, 2) void mlp_kernel(MlpArgs A) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kMlpSmem];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r = lane & 15, q = lane >> 4;
   WaveTiles &L = ((WaveTiles *)smem)[wv];
   const int64_t nchunk = (A.n + 31) / 32;
-  const u32x4 *Fg = A.frag + lane;
+  // fragment id and bias o + r: a buffer descriptor, one 32-bit lane offset and a
+  // constant, not a 64-bit address each
+  const auto rf = buf_rsrc(A.frag), rw = buf_rsrc(A.w);
+  const auto frag = [&](int id) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rf, (uint32_t)lane * 16u, id * 1024, 0));
+  };
+  const auto bias_of = [&](int o) { return buf_load<float>(rw, (uint32_t)r * 4u, o * 4); };
 
   for (int e = lane; e < 32 * 16; e += 64) L.d3[e] = 0;
   f4v gw1[4], gw2[16], gw3[4];
@@ -347,18 +360,19 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
       ax[mt] = a;
       if (TRAIN && q < 2) *(u32x4 *)&L.xs[(16 * mt + r) * 16 + 8 * q] = a;
     }
-    f4v z1[2][4];
+    uint32_t on1 = 0, on2 = 0;  // where z1, z2 > 0: bit 16 mt + 4 nt + i
 #pragma unroll
     for (int nt = 0; nt < 4; nt++) {
-      const u32x4 bw = Fg[(kFragW1 + nt) * 64];
-      const float bias = A.w[kOffB1 + 16 * nt + r];
+      const u32x4 bw = frag(kFragW1 + nt);
+      const float bias = bias_of(kOffB1 + 16 * nt);
 #pragma unroll
       for (int mt = 0; mt < 2; mt++) {
-        z1[mt][nt] = mma(ax[mt], bw, f4v{0.0f, 0.0f, 0.0f, 0.0f});
+        const f4v z1 = mma(ax[mt], bw, f4v{0.0f, 0.0f, 0.0f, 0.0f});
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          z1[mt][nt][i] += bias;
-          L.ha[(16 * mt + 4 * q + i) * kRow + 16 * nt + r] = (uint16_t)bf16_bits(fmaxf(z1[mt][nt][i], 0.0f));
+          const float z = z1[i] + bias;
+          if (TRAIN) on1 |= z > 0.0f ? 1u << (16 * mt + 4 * nt + i) : 0u;
+          L.ha[(16 * mt + 4 * q + i) * kRow + 16 * nt + r] = (uint16_t)bf16_bits(fmaxf(z, 0.0f));
         }
       }
     }
@@ -373,7 +387,7 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
     for (int kt = 0; kt < 2; kt++) {
       u32x4 bw[4];
 #pragma unroll
-      for (int nt = 0; nt < 4; nt++) bw[nt] = Fg[(kFragW2 + 4 * kt + nt) * 64];
+      for (int nt = 0; nt < 4; nt++) bw[nt] = frag(kFragW2 + 4 * kt + nt);
 #pragma unroll
       for (int mt = 0; mt < 2; mt++) {
         const u32x4 a = *(const u32x4 *)&L.ha[(16 * mt + r) * kRow + 32 * kt + 8 * q];
@@ -383,13 +397,14 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
     }
 #pragma unroll
     for (int nt = 0; nt < 4; nt++) {
-      const float bias = A.w[kOffB2 + 16 * nt + r];
+      const float bias = bias_of(kOffB2 + 16 * nt);
 #pragma unroll
       for (int mt = 0; mt < 2; mt++)
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          z2[mt][nt][i] += bias;
-          L.hb[(16 * mt + 4 * q + i) * kRow + 16 * nt + r] = (uint16_t)bf16_bits(fmaxf(z2[mt][nt][i], 0.0f));
+          const float z = z2[mt][nt][i] + bias;
+          if (TRAIN) on2 |= z > 0.0f ? 1u << (16 * mt + 4 * nt + i) : 0u;
+          L.hb[(16 * mt + 4 * q + i) * kRow + 16 * nt + r] = (uint16_t)bf16_bits(fmaxf(z, 0.0f));
         }
     }
     __syncthreads();
@@ -398,13 +413,13 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
       f4v z3[2] = {f4v{0.0f, 0.0f, 0.0f, 0.0f}, f4v{0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
       for (int kt = 0; kt < 2; kt++) {
-        const u32x4 bw = Fg[(kFragW3 + kt) * 64];
+        const u32x4 bw = frag(kFragW3 + kt);
 #pragma unroll
         for (int mt = 0; mt < 2; mt++)
           z3[mt] = mma(*(const u32x4 *)&L.hb[(16 * mt + r) * kRow + 32 * kt + 8 * q], bw, z3[mt]);
       }
       if (r < 3) {
-        const float bias = A.w[kOffB3 + r];
+        const float bias = bias_of(kOffB3);
 #pragma unroll
         for (int mt = 0; mt < 2; mt++)
 #pragma unroll
@@ -478,10 +493,10 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
       const u32x4 a = (q == 0) ? *(const u32x4 *)&L.d3[(16 * mt + r) * 16] : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
       for (int nt = 0; nt < 4; nt++) {
-        const f4v dh = mma(a, Fg[(kFragW3T + nt) * 64], f4v{0.0f, 0.0f, 0.0f, 0.0f});
+        const f4v dh = mma(a, frag(kFragW3T + nt), f4v{0.0f, 0.0f, 0.0f, 0.0f});
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          dz[mt][nt][i] = z2[mt][nt][i] > 0.0f ? dh[i] : 0.0f;
+          dz[mt][nt][i] = (on2 >> (16 * mt + 4 * nt + i) & 1u) ? dh[i] : 0.0f;
           gb2[nt] += dz[mt][nt][i];
         }
       }
@@ -515,7 +530,7 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
     for (int kt = 0; kt < 2; kt++) {
       u32x4 bw[4];
 #pragma unroll
-      for (int nt = 0; nt < 4; nt++) bw[nt] = Fg[(kFragW2T + 4 * kt + nt) * 64];
+      for (int nt = 0; nt < 4; nt++) bw[nt] = frag(kFragW2T + 4 * kt + nt);
 #pragma unroll
       for (int mt = 0; mt < 2; mt++) {
         const u32x4 a = *(const u32x4 *)&L.hb[(16 * mt + r) * kRow + 32 * kt + 8 * q];
@@ -529,7 +544,7 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
       for (int nt = 0; nt < 4; nt++)
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-          dz[mt][nt][i] = z1[mt][nt][i] > 0.0f ? dz[mt][nt][i] : 0.0f;
+          dz[mt][nt][i] = (on1 >> (16 * mt + 4 * nt + i) & 1u) ? dz[mt][nt][i] : 0.0f;
           gb1[nt] += dz[mt][nt][i];
         }
     __syncthreads();
@@ -566,9 +581,10 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
     gb3[2] += __shfl_xor(gb3[2], m);
     gloss += __shfl_xor(gloss, m);
   }
-  float *red = (float *)smem;
-  for (int w = 0; w < 4; w++) {
-    if (wv == w) {
+  // waves 0 and 1 store their sums side by side, waves 2 and 3 add theirs
+  float *red = (float *)smem + (wv & 1) * kMlpPartStride;
+  for (int w = 0; w < 2; w++) {
+    if (wv >> 1 == w) {
       auto put = [&](int idx, float v) { red[idx] = (w == 0) ? v : red[idx] + v; };
 #pragma unroll
       for (int nt = 0; nt < 4; nt++)
@@ -602,7 +618,9 @@ __global__ __launch_bounds__(256) void mlp_kernel(MlpArgs A) {
     }
     __syncthreads();
   }
-  for (int p = threadIdx.x; p <= kMlpParams; p += blockDim.x) A.part[(int64_t)blockIdx.x * kMlpPartStride + p] = red[p];
+  const float *r0 = (const float *)smem;
+  for (int p = threadIdx.x; p <= kMlpParams; p += blockDim.x)
+    A.part[(int64_t)blockIdx.x * kMlpPartStride + p] = r0[p] + r0[kMlpPartStride + p];
 }
 
 // Sum of the workgroup partials in FP64 in a fixed order (kSlices runs of

@@ -100,7 +100,8 @@ __global__ void finalize_kernel(const MeshDev *__restrict__ meshes, int n_meshes
 // run at once and every load but the flux slots' is independent; face after face
 // with a barrier between and the CFL limits in a second pass it was a chain of
 // up to a dozen loads.  Launch times, then and now: 264 blocks of 8^3, FP32, 10.3
-// and 7.4 us; 80 blocks of 16^3, FP64, 18.5 and 11.2 us.
+// and 7.4 us; the 16^3 blocks around a ball refined once in 6^3 trees, FP64, 18.5
+// and 11.2 us.
 template <typename T, int NDIM, int NV>
 __global__ __launch_bounds__(256) void fluxfix_kernel(const MeshDev *__restrict__ Mp, int stage, int parts,
                                                       SubStep ss) {
