@@ -36,9 +36,11 @@ static bool srl_x_by_block(const foap4_mesh *m) { return m->d.ndim == 3 && m->d.
 // LDS), and a round of r <= S items takes about (r + 1.25 S) / (2.25 S) of a
 // full one, because few waves wait more on their own chains.  An item costs
 // its planes plus two (the planes around a slab are loaded and converted
-// again).  The least of rounds x planes is taken.  Measured, two Heun steps in
-// us by planes per item (the choice marked): FP32 180 blocks of 16^3: 163 (16),
-// 126 (8), 102 (4)*, 105 (2); 512 blocks: 190 (16), 152 (8)*, 173 (4); 720: 211
+// again).  The least of rounds x planes is taken; where block sizes are mixed, of
+// the mean item's, plus what the longest exceeds it by (38,540 blocks of 8^3, 16^3
+// and 32^3: 14.1 ms a step whole*, 14.6 with 16 planes per item).  Measured, two
+// Heun steps in us by planes per item (the choice marked): FP32 180 blocks of
+// 16^3: 163 (16), 126 (8), 102 (4)*, 105 (2); 512 blocks: 190 (16), 152 (8)*, 173 (4); 720: 211
 // (16)*, 219 (8); 80 blocks of 32^3: 327 (32), 219 (16)*, 218 (8), 235 (4); one:
 // 275 (32), 52 (1)*; FP64 180 of 16^3: 204 (16), 162 (8)*, 176 (4); 27 of 32^3:
 // 204 (16), 156 (8)*, 196 (4); 512 of 8^3: FP32 96 (8), 82 (4), 85 (2)*.
@@ -53,14 +55,17 @@ static int slab_planes(foap4_mesh *const *meshes, size_t n_meshes, int n_cu) {
   int best = largest;
   double best_cost = 0.0;
   for (int kd = largest; kd >= 1; kd /= 2) {
-    int64_t items = 0;
+    int64_t items = 0, planes = 0;
     for (size_t i = 0; i < n_meshes; i++) {
       const int N = meshes[i]->d.block_n;
-      items += stage_items_for(3, N, (int64_t)meshes[i]->topo.leaves.size(), std::max(1, N / kd));
+      const int64_t it = stage_items_for(3, N, (int64_t)meshes[i]->topo.leaves.size(), std::max(1, N / kd));
+      items += it;
+      planes += it * (std::min(N, kd) + 2);
     }
     const int64_t n = (items + n_cu - 1) / n_cu, full = n / at_once, rest = n % at_once;
     const double rounds = (double)full + (rest ? (rest + 1.25 * at_once) / (2.25 * at_once) : 0.0);
-    const double cost = rounds * (kd + 2);
+    const double mean = items ? (double)planes / items : 0.0;
+    const double cost = rounds * mean + (kd + 2 - mean);
     if (kd == largest || cost < best_cost) {
       best = kd;
       best_cost = cost;
