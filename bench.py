@@ -49,13 +49,11 @@ def stage_bytes_per_cell(S, N=16):
     return (2.5 + halo_share(N)) * S
 
 
-def step_bytes_per_update(S, gather, N=16):
-    """Whole step per cell update.  Gathered halos on a mesh without
-    refinement boundaries (the batched form): no ghost fill, (2.5 + h) S.
-    Stored ghosts (the paper's design, the plain form): each stage's ghost
-    fill also reads and writes h S, (2.5 + 3 h) S (4.75 S at N = 16)."""
-    h = halo_share(N)
-    return (2.5 + h if gather else 2.5 + 3.0 * h) * S
+def step_bytes_per_update(S, N=16):
+    """Whole step per cell update on a mesh without refinement boundaries:
+    both forms read same-level halos from the neighbours, so there is no ghost
+    fill, and the step moves what its two stages move, (2.5 + h) S."""
+    return (2.5 + halo_share(N)) * S
 
 
 def parse_config(text):
@@ -240,7 +238,7 @@ def main():
                 torch.cuda.empty_cache()
             log("profile run done")
             return
-        if args.profile_workload == "noise_shear_fp64_plain":  # three plain FP64 steps (stored ghosts)
+        if args.profile_workload == "noise_shear_fp64_plain":  # three plain FP64 steps
             m = make(f4.F64)
             m.step(3)
             torch.cuda.synchronize()
@@ -293,7 +291,7 @@ def main():
     log("phases (ms):", json.dumps({k: round(v, 4) for k, v in phases.items()}))
     stage_bytes = cells * stage_bytes_per_cell(S32, args.block)
     achieved = stage_bytes / (phases["stage"] * 1e-3) / 1e9
-    step_gbs = gcups32 * step_bytes_per_update(S32, True, args.block)
+    step_gbs = gcups32 * step_bytes_per_update(S32, args.block)
 
     result = {
         "metric": METRIC,
@@ -319,7 +317,7 @@ def main():
                                                        stage_bytes) if (args.block, args.n) == (16, 256) else None),
                      "kernel": f"stage_kernel<float,3,N={args.block}>", "bytes_per_launch": int(stage_bytes),
                      "avg_launch_ms": round(phases["stage"], 5)},
-        "step_hbm": {"bytes_per_update": step_bytes_per_update(S32, True, args.block), "achieved_gbs": round(step_gbs, 1),
+        "step_hbm": {"bytes_per_update": step_bytes_per_update(S32, args.block), "achieved_gbs": round(step_gbs, 1),
                      "frac": round(step_gbs / HBM_PEAK_GBS, 4)},
         "phases_ms": {k: round(v, 5) for k, v in phases.items()},
         "repeats": {"timed_regions": len(rep_ms), "ms_per_step_min": round(rep_ms[0], 4),
@@ -331,7 +329,7 @@ def main():
     torch.cuda.empty_cache()
 
     if not args.skip_fp64:
-        # ---------------- FP64 plain: one workgroup per block, stored ghosts, one launch per kernel
+        # ---------------- FP64 plain: one launch per kernel and mesh, no graph
         m64 = make(f4.F64)
         m64.step(args.warmup)
         secs64, _ = timed_steps(lambda n: m64.step(n), args.steps, torch.cuda.synchronize)
@@ -339,7 +337,7 @@ def main():
         log(f"FP64 plain: {secs64 / args.steps * 1e3:.3f} ms/step, {gcups64:.2f} Gcell-updates/s")
         result["fp64_plain"] = {"value": round(gcups64, 4), "unit": "Gcell-updates/s",
                                 "ms_per_step": round(secs64 / args.steps * 1e3, 4),
-                                "step_hbm_frac": round(gcups64 * step_bytes_per_update(S64, False, args.block) / HBM_PEAK_GBS, 4),
+                                "step_hbm_frac": round(gcups64 * step_bytes_per_update(S64, args.block) / HBM_PEAK_GBS, 4),
                                 "batched_fp32_over_plain_fp64": round(gcups32 / gcups64, 3)}
         del m64
         torch.cuda.empty_cache()
@@ -353,7 +351,7 @@ def main():
         log(f"FP64 batched: {secs64b / args.steps * 1e3:.3f} ms/step, {gcups64b:.2f} Gcell-updates/s")
         result["fp64_batched"] = {"value": round(gcups64b, 4), "unit": "Gcell-updates/s",
                                   "ms_per_step": round(secs64b / args.steps * 1e3, 4), "config": list(cfg64),
-                                  "step_hbm_frac": round(gcups64b * step_bytes_per_update(S64, True, args.block) / HBM_PEAK_GBS, 4)}
+                                  "step_hbm_frac": round(gcups64b * step_bytes_per_update(S64, args.block) / HBM_PEAK_GBS, 4)}
         del b64, m64
         torch.cuda.empty_cache()
 
@@ -395,7 +393,7 @@ def main():
                                                                  "stage_traffic_rayleigh_taylor_256cubed_b16.json"),
                                                     r"stage_kernel<float, 3, 2, [12], 5>", stage_bytes)
                               if (args.block, args.n) == (16, 256) else None),
-            "step_hbm_frac": round(g_rt * step_bytes_per_update(S32, True, args.block) / HBM_PEAK_GBS, 4),
+            "step_hbm_frac": round(g_rt * step_bytes_per_update(S32, args.block) / HBM_PEAK_GBS, 4),
             "fp64_plain": {"value": round(g_rt64, 4), "ms_per_step": round(sr64 / args.steps * 1e3, 4)},
             "paper_h100_context": (None if paper is None or args.n != 256 else
                                    {"fp32": paper[0], "fp64": paper[1],
@@ -460,9 +458,9 @@ def main():
                 "dtype": "f32", "ms_per_step": round(ss_ / args.steps * 1e3, 4), "config": list(cfg_s),
                 "stage_ms": round(ph_s["stage"], 5),
                 "stage_hbm_frac": round(sb / (ph_s["stage"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                "step_hbm_frac": round(g_s * step_bytes_per_update(S32, True, nb_) / HBM_PEAK_GBS, 4),
+                "step_hbm_frac": round(g_s * step_bytes_per_update(S32, nb_) / HBM_PEAK_GBS, 4),
                 "fp64_plain": {"value": round(g_s64, 4), "ms_per_step": round(ss64 / args.steps * 1e3, 4),
-                               "step_hbm_frac": round(g_s64 * step_bytes_per_update(S64, False, nb_) / HBM_PEAK_GBS,
+                               "step_hbm_frac": round(g_s64 * step_bytes_per_update(S64, nb_) / HBM_PEAK_GBS,
                                                       4)},
                 "paper_h100_context_rt": (None if paper_s is None else
                                           {"fp32": paper_s[0], "fp64": paper_s[1],
@@ -504,8 +502,8 @@ def main():
                   fluxfix_share=round(ph_tl["fluxfix"] / ph_tl["step"], 4))
         del bt, m
         torch.cuda.empty_cache()
-        # the other three forms: FP32 plain (per-kernel launches, stored
-        # ghosts), FP64 plain (the paper's form) and FP64 batched (the FP32
+        # the other three forms: FP32 plain (per-kernel launches),
+        # FP64 plain (the same) and FP64 batched (the FP32
         # leg's launch configuration, not tuned for FP64)
         for prec, form in ((f4.F32, "fp32_plain"), (f4.F64, "fp64_plain"), (f4.F64, "fp64_batched")):
             m = make_tl(prec)
@@ -569,9 +567,9 @@ def main():
                 "stage_ms": round(pha["stage"], 5), "ghost_r1_ms": round(pha["ghost_r1"], 5),
                 "stage_bytes_per_launch": int(adv_stage_bytes),
                 "stage_hbm_frac": round(adv_gbs / HBM_PEAK_GBS, 4),
-                "step_hbm_frac": round(ga * step_bytes_per_update(4, False, args.block) / HBM_PEAK_GBS, 4),
+                "step_hbm_frac": round(ga * step_bytes_per_update(4, args.block) / HBM_PEAK_GBS, 4),
                 "fp64_plain": {"value": round(ga64, 4), "ms_per_step": round(sa64 / args.steps * 1e3, 4),
-                               "step_hbm_frac": round(ga64 * step_bytes_per_update(8, False, args.block)
+                               "step_hbm_frac": round(ga64 * step_bytes_per_update(8, args.block)
                                                       / HBM_PEAK_GBS, 4)},
                 "paper_h100_context": (None if paper_a is None else
                                        {"fp64": paper_a, "source": "table of results on uniform grids, "
@@ -579,7 +577,7 @@ def main():
             log(f"advection {n_adv}^3: FP32 batched {ga:.2f}, FP64 plain {ga64:.2f} Gcell-updates/s, "
                 f"stage {pha['stage']:.4f} ms")
         result["advection"] = dict(adv, workload="advection_sphere_b16", scheme="van Leer, Rusanov, Heun, "
-                                                                              "v = (1, 1, 1), stored ghosts")
+                                                                              "v = (1, 1, 1)")
 
     # ---------------- the 64-problem batch (mixed 8^3/16^3/32^3 blocks), FP32
     if not args.skip_batch64:
@@ -592,7 +590,7 @@ def main():
             ms.append(m)
         cells64 = sum(int(np.prod(wp["trees"])) * wp["N"] ** 3 for wp in ws)
         # algorithmic bytes per update, cell-weighted over the problems' block sizes
-        bpu64 = sum(int(np.prod(wp["trees"])) * wp["N"] ** 3 * step_bytes_per_update(S32, True, wp["N"])
+        bpu64 = sum(int(np.prod(wp["trees"])) * wp["N"] ** 3 * step_bytes_per_update(S32, wp["N"])
                     for wp in ws) / cells64
         b64 = f4.Batch(ms)
         cfg = b64.autotune(args.tune_cache)

@@ -314,8 +314,8 @@ constexpr int kMlpSmem = (4 * (int)sizeof(WaveTiles) > (2 * kMlpPartStride * 4))
 // them in one pass, which takes 256 registers or less: where z1 and z2 are
 // positive is kept as a bit each, not the values, and fragments and biases are
 // addressed by descriptors (a hoisted 64-bit address each took 70 registers).
-// One loss and gradient of 64,510 rows: 75 us at 364 registers and one
-// workgroup a CU, 59 now, 57 with the waves' sums added in two turns, not four.
+// At 64,510 rows: 39 us at 364 registers and one workgroup a CU, 23 now (2 us of
+// it by adding the waves' sums in two turns, not four).
 template <bool TRAIN>
 __global__ __launch_bounds__(256, 2) void mlp_kernel(MlpArgs A) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kMlpSmem];
