@@ -294,6 +294,7 @@ int64_t stage_items_for(int ndim, int N, int64_t nb, int ks);
 // nmask: block sizes present in the launch (1: N = 8, 2: N = 16, 4: N = 32);
 // scheme: scheme_of() of the meshes in the launch; stage 1 / 2: Heun's stages,
 // stage 3: the generic sub-step ss, stage 4: the same with three earlier states
+constexpr int kLastFirst = 4;  // in xcd: the items from the last to the first
 hipError_t launch_stage(const MeshDev *d_meshes, int n_meshes, int64_t total_items, int stage,
                         int ndim, bool f64, int grid, hipStream_t s, int xcd, int nmask, int scheme,
                         const SubStep &ss = SubStep{});

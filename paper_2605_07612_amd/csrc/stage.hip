@@ -567,6 +567,7 @@ __device__ __forceinline__ void stage_item(const MeshDev &M, int stage, int64_t 
 // takes the w-th contiguous chunk, so a block and its Morton neighbours (the
 // x neighbour first) run back to back on one CU and the neighbour rows that a
 // halo read pulls into the cache are used again by the next item.
+// (kLastFirst in a launch's order turns the range round.)
 __device__ __forceinline__ int64_t item_of(int64_t w, int64_t it, int64_t grid, int64_t total, int xcd) {
   if (!xcd) return w + it * grid;
   if (xcd == 2) return w * ((total + grid - 1) / grid) + it;
@@ -597,8 +598,9 @@ constexpr int stage_waves() {
 // same with three earlier states (classical RK4's last sub-step)
 template <typename T, int NDIM, int NM, int STG, int SCH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(stage_waves<T, NM, STG>())))
-void stage_kernel(const MeshDev *__restrict__ meshes, int n_meshes, int64_t total, int xcd, SubStep ss) {
+void stage_kernel(const MeshDev *__restrict__ meshes, int n_meshes, int64_t total, int order, SubStep ss) {
   constexpr int stage = STG;
+  const int xcd = order & 3;
   __shared__ T smem[smem_cells<NDIM, NM, (int)sizeof(T)>()];
   double vmax = 0.0;
   bool bad = false;
@@ -607,8 +609,9 @@ void stage_kernel(const MeshDev *__restrict__ meshes, int n_meshes, int64_t tota
   const int64_t lanes = grid / 8 > 0 ? grid / 8 : 1;
   const int64_t iters = xcd == 1 ? ((total + 7) / 8 + lanes - 1) / lanes : (total + grid - 1) / grid;
   for (int64_t it = 0; it < iters; it++) {
-    const int64_t item = item_of(blockIdx.x, it, grid, total, xcd);
+    int64_t item = item_of(blockIdx.x, it, grid, total, xcd);
     if (item >= total) break;
+    if (order & kLastFirst) item = total - 1 - item;
     int lo = 0, hi = n_meshes - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -681,7 +684,7 @@ template <int SCH>
 hipError_t launch_stage_sch(const MeshDev *d_meshes, int n_meshes, int64_t total_items, int stage, int ndim,
                             bool f64, int grid, hipStream_t s, int xcd, int nmask, const SubStep &ss) {
   int64_t nblk = (grid > 0 && grid < total_items) ? grid : total_items;
-  if (xcd == 1) nblk = (nblk + 7) / 8 * 8;  // every XCD gets the same number of workgroups
+  if ((xcd & 3) == 1) nblk = (nblk + 7) / 8 * 8;  // every XCD gets the same number of workgroups
   if (f64) {
     if (ndim == 3) launch_t<double, 3, SCH>((unsigned)nblk, nmask, d_meshes, n_meshes, total_items, stage, xcd, s, ss);
     else launch_t<double, 2, SCH>((unsigned)nblk, nmask, d_meshes, n_meshes, total_items, stage, xcd, s, ss);

@@ -340,6 +340,30 @@ def test_slab_depths(f4, N, trees, prec):
     assert err <= TOL[prec]
 
 
+@pytest.mark.parametrize("N,trees,prec", [(16, (10, 11, 11), 0), (16, (10, 11, 12), 0), (16, (7, 8, 11), 1),
+                                          (32, (5, 5, 7), 0)])
+def test_second_stage_from_the_last_item(f4, N, trees, prec):
+    """Meshes on either side of the line (96 MiB: FP32 1229 blocks of 16^3, 154
+    of 32^3, FP64 615 of 16^3) from which the second stage runs its items from
+    the last to the first: two steps in the plain form against the oracle, and
+    batched in every item order, in one workgroup per item and in few."""
+    w = small_uniform(N, trees)
+    gp, om = build_pair(w, prec)
+    gp.step(2)
+    om.step(2)
+    a = interior(gpu_state(gp), 2, N, 3)
+    err, _ = check_state(a, om.interior(), gp.export()[0], 3, w["tree_size"], N, prec)
+    say(w["name"], "prec", prec, "rel L1", err)
+    assert err <= TOL[prec]
+    for order, wg in ((0, 0), (1, 0), (1, 3), (2, 2)):
+        gb, _ = build_pair(w, prec)
+        b = f4.Batch([gb])
+        b.set_config(1, wg, order, 1)
+        b.step(2)
+        assert np.array_equal(interior(gpu_state(gb), 2, N, 3), a), (order, wg)
+        b.close()
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 def test_batch_follows_regrid(f4, prec):
     """A batch keeps working across a regrid of its mesh (new leaf table,
