@@ -3,31 +3,11 @@
 // (Sec. 2.7).
 #include "device_common.h"
 #include "foap4_internal.h"
+#include "stage_common.h"
 
 #include <mutex>
 
 namespace f4 {
-
-// sum_d (|v_d| + c) / dx of one cell in FP64, operation order of the
-// definition, no contraction (bit-identical to a plain evaluation).
-template <int NDIM>
-__device__ __forceinline__ double inv_dt_cell(const double *U, double gamma, double dx, bool &bad) {
-#pragma clang fp contract(off)
-  const double r = U[0];
-  double ke = 0.0, v[3];
-#pragma unroll
-  for (int d = 0; d < NDIM; d++) {
-    v[d] = U[1 + d] / r;
-    ke += U[1 + d] * v[d];
-  }
-  const double p = (gamma - 1.0) * (U[NDIM + 1] - 0.5 * ke);
-  const double cs = sqrt(gamma * p / r);
-  double s = 0.0;
-#pragma unroll
-  for (int d = 0; d < NDIM; d++) s += (fabs(v[d]) + cs) / dx;
-  bad |= !(r > 0.0) || !(p > 0.0) || !isfinite(s);
-  return s;
-}
 
 // Scalar advection (Sec. 3.4): the fastest wave along d is |v_d| in every
 // cell, so the CFL limit is sum_d |v_d| / dx (the definition's operation
@@ -71,7 +51,7 @@ __global__ __launch_bounds__(256) void dt_full_kernel(const MeshDev *__restrict_
 #pragma unroll
     for (int v = 0; v < NV; v++) U[v] = (double)u[v * sv + o];
     if constexpr (NV == 1) vmax = fmax(vmax, inv_dt_adv<NDIM>(M, U[0], dx, bad));
-    else vmax = fmax(vmax, inv_dt_cell<NDIM>(U, M.gamma, dx, bad));
+    else vmax = fmax(vmax, cell_inv_dt<NDIM>(U, M.gamma, dx, bad));
   }
   wave_flush(M.scal, vmax, bad);
 }
@@ -176,7 +156,7 @@ __global__ __launch_bounds__(256) void fluxfix_kernel(const MeshDev *__restrict_
 #pragma unroll
       for (int v = 0; v < NV; v++) U[v] = (double)u[v];
       if constexpr (NV == 1) vmax = fmax(vmax, inv_dt_adv<NDIM>(M, U[0], dx, bad));
-      else vmax = fmax(vmax, inv_dt_cell<NDIM>(U, M.gamma, dx, bad));
+      else vmax = fmax(vmax, cell_inv_dt<NDIM>(U, M.gamma, dx, bad));
     }
   }
   if (limit) wave_flush(M.scal, vmax, bad);

@@ -531,7 +531,7 @@ __device__ __forceinline__ void stage_item(const MeshDev &M, int stage, int64_t 
       const bool skip = f2c_adj || (f2c_zlo && k == 0) || (f2c_zhi && k == N - 1);
       if (!skip) {
         if constexpr (sizeof(T) == 8) {
-          vloc = fmax(vloc, cell_inv_dt<NDIM>((const double *)Uout, M.gamma, (double)idx, bad));
+          vloc = fmax(vloc, cell_inv_dt<NDIM>((const double *)Uout, M.gamma, dx, bad));
         } else {
           vloc = fmaxf(vloc, cell_inv_dt<NDIM>((const float *)Uout, (float)gamma, (float)idx, bad));
         }

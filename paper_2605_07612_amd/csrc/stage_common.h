@@ -7,27 +7,30 @@
 
 namespace f4 {
 
-// CFL inverse time step sum_d (|v_d| + c) / dx of one cell, with one
-// reciprocal of the density and the inverse cell width: FP64 states with the
-// refined reciprocal and square root (a few ulp; the IEEE divisions and root
-// of the plain evaluation cost 136 instructions a cell, a fifth of the stage),
-// FP32 states in FP32 with the hardware ones.  The maximum over cells is
-// reduced in FP64 (an FP32 maximum converts exactly, so a kernel may keep its
-// running maximum in FP32).
+// CFL inverse time step sum_d (|v_d| + c) / dx of one cell.  FP64: the
+// operation order of the definition, IEEE divisions and root, no contraction
+// (bit-identical to a plain evaluation).  The stage epilogues, the flux fix and
+// the standalone reduction all use it, so a state's dt does not depend on which
+// of them found it.  It is a fifth of an FP64 stage's instructions (136 a cell):
+// a refined reciprocal and root in their place gave dt an ulp or two off.
+// FP32 states in the stage epilogues: FP32 with the hardware reciprocal and
+// root.  The maximum over cells is reduced in FP64 (an FP32 maximum converts
+// exactly, so a kernel may keep its running maximum in FP32).
 template <int NDIM>
-__device__ __forceinline__ double cell_inv_dt(const double *U, double gamma, double idx, bool &bad) {
+__device__ __forceinline__ double cell_inv_dt(const double *U, double gamma, double dx, bool &bad) {
+#pragma clang fp contract(off)
   const double r = U[0];
-  const double ir = rcp_nr(r);
-  double ke = 0.0, sv = 0.0;
+  double ke = 0.0, v[3];
 #pragma unroll
   for (int d = 0; d < NDIM; d++) {
-    const double v = U[1 + d] * ir;
-    ke += U[1 + d] * v;
-    sv += fabs(v);
+    v[d] = U[1 + d] / r;
+    ke += U[1 + d] * v[d];
   }
   const double p = (gamma - 1.0) * (U[NDIM + 1] - 0.5 * ke);
-  const double cs = sqrt_nr(gamma * p * ir);
-  const double s = (sv + NDIM * cs) * idx;
+  const double cs = sqrt(gamma * p / r);
+  double s = 0.0;
+#pragma unroll
+  for (int d = 0; d < NDIM; d++) s += (fabs(v[d]) + cs) / dx;
   bad |= !(r > 0.0) || !(p > 0.0) || !isfinite(s);
   return s;
 }

@@ -442,7 +442,7 @@ __global__ __launch_bounds__(TS *TS) void weno_kernel(const MeshDev *__restrict_
     }
     // cells next to F2C faces are finished (and their dt taken) by the flux fix
     if ((STG == 2 || (STG >= 3 && ss.epi)) && !(skip_xy || (skip_lo && k == 0) || (skip_hi && k == N - 1))) {
-      if constexpr (sizeof(T) == 8) vloc = fmax(vloc, cell_inv_dt<NDIM>((const double *)Uout, M.gamma, (double)idx, bad));
+      if constexpr (sizeof(T) == 8) vloc = fmax(vloc, cell_inv_dt<NDIM>((const double *)Uout, M.gamma, dx, bad));
       else vloc = fmaxf(vloc, cell_inv_dt<NDIM>((const float *)Uout, (float)gamma, (float)idx, bad));
     }
     if constexpr (NDIM == 3) {

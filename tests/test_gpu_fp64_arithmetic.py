@@ -1,0 +1,74 @@
+"""The FP64 arithmetic of the stage kernels at single-operation accuracy.
+Every expectation is exact (no tolerance)."""
+import sys
+
+import numpy as np
+import pytest
+
+import synth
+from tests.gpu_helpers import build_pair, gpu_state, interior
+from tests.test_gpu_parity import small_uniform
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def f4():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2605_07612_amd as f4
+    f4.lib()
+    return f4
+
+
+CFL_CASES = {
+    "8": small_uniform(8, (4, 3, 2)),
+    "16": small_uniform(16, (3, 2, 1)),
+    "32": small_uniform(32, (1, 2, 1)),
+    "2d": small_uniform(16, (3, 2), ndim=2),
+    "vanleer-hll": dict(small_uniform(16, (2, 2, 2)), limiter="vanleer", flux="hll"),
+    "gravity": dict(small_uniform(16, (2, 2, 2)), gravity=(0.0, 0.1, -0.2)),
+    "weno5": dict(small_uniform(16, (2, 2, 1)), limiter="weno5", g=3),
+    "weno5-2d": dict(small_uniform(8, (3, 2), ndim=2), limiter="weno5", g=3),
+    "two-level": synth.two_level_blast(base_trees=4, block=8),
+}
+
+
+@pytest.mark.parametrize("form", ["plain", "batch"])
+@pytest.mark.parametrize("name", list(CFL_CASES))
+def test_step_dt_is_the_plain_evaluation(f4, name, form):
+    """The time step that a step leaves behind (the CFL limits of the stage
+    epilogue and the flux fix) is the one that foap4_compute_dt and the
+    oracle's plain FP64 evaluation give for the same state, bit for bit."""
+    w = CFL_CASES[name]
+    gm, om = build_pair(w, 1)
+    b = f4.Batch([gm]) if form == "batch" else None
+    for step in range(3):
+        (b or gm).step(1)
+        left = gm.time()[1]
+        om.u[...] = 0.0
+        om.interior()[...] = interior(gpu_state(gm), w["g"], w["N"], w["ndim"])
+        plain = om.dt()
+        gm.compute_dt()
+        say("step dt", name, form, step, left.hex(), gm.time()[1].hex(), plain.hex())
+        assert left == plain
+        assert gm.time()[1] == plain
+
+
+@pytest.mark.parametrize("integrator", ["ssprk3", "ssprk43", "rk4"])
+def test_step_dt_of_the_other_integrators(f4, integrator):
+    w = small_uniform(16, (2, 2, 1))
+    from paper_2605_07612_amd import layout
+    gm = f4.Mesh(3, w["trees"], 16, 2, w["tree_size"], prec=f4.F64, gamma=w["gamma"], cfl=w["cfl"],
+                 integrator=integrator)
+    layout.set_from_field(gm, w["field"])
+    gm.step(2)
+    left = gm.time()[1]
+    gm.compute_dt()
+    assert left == gm.time()[1]
