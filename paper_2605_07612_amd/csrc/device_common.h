@@ -68,13 +68,6 @@ __device__ __forceinline__ double rsq_nr(double x) {
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// FP64 square root of x >= 0 (NaN below zero): x / sqrt(x).  The shift, far
-// below one ulp of any x above 1e-284, keeps a zero from becoming 0 inf.
-__device__ __forceinline__ double sqrt_nr(double x) {
-  x += 1e-300;
-  return x * rsq_nr(x);
-}
-
 // sqrt(r) and 1/sqrt(r) of a positive, normal density.
 __device__ __forceinline__ void sqrt_and_rsq(float r, float &s, float &q) {
   q = __builtin_amdgcn_rsqf(r);
@@ -154,7 +147,7 @@ __device__ __forceinline__ void einfeldt(double rl, double rr, double vl, double
   const double ia = b * r, ib = a * r;
   ubar = (rl * vl + g * vr) * ia;
   const double dv = vr - vl;
-  db = sqrt_nr(gamma * (pl * ia + pr * ib) + (0.5 * m) * r * (dv * dv));
+  db = fsqrt(gamma * (pl * ia + pr * ib) + (0.5 * m) * r * (dv * dv));
 }
 
 // Numerical flux (Sec. 3.2) along axis AX between reconstructed primitive

@@ -72,3 +72,39 @@ def test_step_dt_of_the_other_integrators(f4, integrator):
     left = gm.time()[1]
     gm.compute_dt()
     assert left == gm.time()[1]
+
+
+def test_wave_speed_root_is_correctly_rounded(f4):
+    """d_bar of Rusanov's flux is a correctly rounded square root.  A shear
+    layer on a gas at rest, rho = 1, v_z = 0 for x < 1/2 and 1 beyond, leaves
+    one inexact step at a time: every slope is zero, u_bar is zero, sqrt(rho)
+    is one, d_bar = sqrt(gamma p), and the only z-momentum flux of the cells at
+    rest next to the layers is d_bar / 2, so that the first Heun stage leaves
+    (dt / dx) d_bar / 2 in them (dx a power of two).  The energy, and with it
+    p = (gamma - 1) E, differs from row to row in y, where nothing couples the
+    z momenta of cells at rest."""
+    from paper_2605_07612_amd import layout
+    rows, gamma = 64, 1.4
+    m = f4.Mesh(3, (2, rows, 1), 8, 2, 1.0, prec=f4.F64, gamma=gamma)
+    e = 1.0 + np.random.default_rng(5).integers(0, 3 << 20, rows * 8) / (1 << 20)
+
+    def field(x, y, z):
+        vz = (x > 1.0).astype(float)
+        E = e[np.floor(y * 8.0).astype(int)] + 0.5 * vz
+        return np.stack([np.ones_like(x), 0 * x, 0 * x, vz, E])
+
+    layout.set_from_field(m, field)
+    m.compute_dt()
+    dt = m.time()[1]
+    m.step(1)
+    _, G = layout.global_coords(m)
+    u1 = m.interior(state=1 - m.cur).cpu().numpy()  # the first stage's result
+    off = 0
+    for n, g in enumerate(np.asarray(G)):
+        if g[0] == 0:  # the blocks at rest, a layer on either side
+            p = (gamma - 1.0) * e[8 * g[1]:8 * g[1] + 8]
+            want = (dt * 8.0) * (0.5 * np.sqrt(gamma * p))
+            for i in (0, 7):
+                off += int(np.sum(u1[n, 3, :, :, i] != want[None, :]))
+    say("shear layer: cells off the correctly rounded value:", off, "of", rows * 128)
+    assert off == 0
