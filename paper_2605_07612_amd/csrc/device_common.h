@@ -52,25 +52,32 @@ __device__ __forceinline__ double minmod(double a, double b) {
 
 // FP64 reciprocal of a normal, finite x: the hardware estimate r (relative
 // error e = 1 - x r of about 2^-24) refined by one third-order step
-// r (1 + e + e^2), which leaves e^3 and the roundings, a few ulp, at about a
-// third of the instructions of an IEEE division.
+// r (1 + e + e^2), which leaves e^3 and the roundings (2^21 values: at most
+// 1.11e-16, as two Newton-Raphson steps leave), at about a third of the
+// instructions of an IEEE division.
 __device__ __forceinline__ double rcp_nr(double x) {
   const double r = __builtin_amdgcn_rcp(x);
   const double e = fma(-x, r, 1.0);
   return fma(r, fma(e, e, e), r);
 }
 
-// FP64 1/sqrt(x) of a positive, normal x: the hardware estimate y refined by
-// one third-order step y (1 + e/2 + 3 e^2/8), e = 1 - x y^2.
-__device__ __forceinline__ double rsq_nr(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double e = fma(-(x * y), y, 1.0);
-  return fma(y * e, fma(0.375, e, 0.5), y);
-}
-
-// sqrt(r) and 1/sqrt(r) of a positive, normal density.
+// sqrt(r) and 1/sqrt(r) of a positive, normal density: one reciprocal
+// square root and s = r q.  FP64 refines the hardware estimate of 1/sqrt(r)
+// by two Newton-Raphson steps q <- q + (q/2)(1 - r q^2), each of which about
+// doubles the correct bits, so q and s are within a few ulp (the IEEE square
+// root and a refined reciprocal of it cost about twice the instructions).  One
+// third-order step gives the same q, but s with a larger mean error (2^21
+// values: 5.8e-17 against 5.3e-17).
 __device__ __forceinline__ void sqrt_and_rsq(float r, float &s, float &q) {
   q = __builtin_amdgcn_rsqf(r);
+  s = r * q;
+}
+__device__ __forceinline__ void sqrt_and_rsq(double r, double &s, double &q) {
+  double y = __builtin_amdgcn_rsq(r);
+  double e = fma(-(r * y), y, 1.0);
+  y = fma(0.5 * y, e, y);
+  e = fma(-(r * y), y, 1.0);
+  q = fma(0.5 * y, e, y);
   s = r * q;
 }
 
@@ -116,40 +123,6 @@ __device__ __forceinline__ T limit(T a, T b) {
   else return minmod(a, b);
 }
 
-// Einfeldt's mean velocity u_bar and d_bar (Sec. 3.5; see riemann below).
-// FP32: with the weights w = sqrt(rho) / (sL + sR) of each side,
-// u_bar = wL vL + wR vR and d_bar^2 = gamma (pL / sL + pR / sR) / (sL + sR)
-// + wL wR dv^2 / 2 (s c^2 = gamma p / s = gamma p / sqrt(rho)).
-__device__ __forceinline__ void einfeldt(float rl, float rr, float vl, float vr, float pl, float pr, float gamma,
-                                         float &ubar, float &db) {
-  float sl, sr, ql, qr;  // sqrt(rho) and 1 / sqrt(rho) of each side
-  sqrt_and_rsq(rl, sl, ql);
-  sqrt_and_rsq(rr, sr, qr);
-  const float is = frcp(sl + sr);
-  const float wlw = sl * is, wrw = sr * is;
-  ubar = wlw * vl + wrw * vr;
-  const float dv = vr - vl;
-  const float d2 = gamma * (pl * ql + pr * qr) * is + (0.5f * wlw * wrw) * (dv * dv);
-  db = fsqrt(d2);
-}
-// FP64: multiplied out with the geometric mean g = sqrt(rho_L rho_R), so that
-// one square root and one reciprocal serve both sides:
-// sL (sL + sR) = rho_L + g and sR (sL + sR) = rho_R + g, hence
-// u_bar = (rho_L vL + g vR) / (rho_L + g), d_bar^2 = gamma (pL / (rho_L + g)
-// + pR / (rho_R + g)) + wL wR dv^2 / 2, wL wR = rho_L rho_R / ((rho_L + g)
-// (rho_R + g)).  The product of the densities stays normal for densities of
-// 1e-150 to 1e150, which FP32 has no room for.
-__device__ __forceinline__ void einfeldt(double rl, double rr, double vl, double vr, double pl, double pr,
-                                         double gamma, double &ubar, double &db) {
-  // max: two negative densities give NaN as one does, and the state is reported
-  const double m = rl * fmax(rr, 0.0), g = m * rsq_nr(m);
-  const double a = rl + g, b = rr + g, r = rcp_nr(a * b);
-  const double ia = b * r, ib = a * r;
-  ubar = (rl * vl + g * vr) * ia;
-  const double dv = vr - vl;
-  db = fsqrt(gamma * (pl * ia + pr * ib) + (0.5 * m) * r * (dv * dv));
-}
-
 // Numerical flux (Sec. 3.2) along axis AX between reconstructed primitive
 // states WL and WR from the Einfeldt speeds (Sec. 3.5): sqrt(rho)-weighted
 // mean velocity u_bar and
@@ -168,9 +141,21 @@ __device__ __forceinline__ void riemann(const T *WL, const T *WR, T gamma, T *F)
   const T rl = WL[0], rr = WR[0];
   const T pl = WL[NV - 1], pr = WR[NV - 1];
   const T vl = WL[1 + AX], vr = WR[1 + AX];
-  // wave speeds first, so the per-component flux needs few live registers
-  T ubar, db;
-  einfeldt(rl, rr, vl, vr, pl, pr, gamma, ubar, db);
+  // wave speeds first, so the per-component flux needs few live registers;
+  // with the weights w = sqrt(rho) / (sL + sR) of each side,
+  // u_bar = wL vL + wR vR and d_bar^2 = gamma (pL / sL + pR / sR) / (sL + sR)
+  // + wL wR dv^2 / 2 (s c^2 = gamma p / s = gamma p / sqrt(rho)).  The roots are
+  // taken side by side: their product sqrt(rho_L rho_R) would spare one, but in
+  // FP64 it ends the range of the densities at 1e-154 and 1e154
+  T sl, sr, ql, qr;  // sqrt(rho) and 1 / sqrt(rho) of each side
+  sqrt_and_rsq(rl, sl, ql);
+  sqrt_and_rsq(rr, sr, qr);
+  const T is = frcp(sl + sr);
+  const T wlw = sl * is, wrw = sr * is;
+  const T ubar = wlw * vl + wrw * vr;
+  const T dv = vr - vl;
+  const T d2 = gamma * (pl * ql + pr * qr) * is + (T(0.5) * wlw * wrw) * (dv * dv);
+  const T db = fsqrt(d2);
   T al, ar, wl, wr;
   if constexpr (!HLL) {
     // max(|u_bar - d_bar|, |u_bar + d_bar|) with d_bar >= 0 is |u_bar| + d_bar,
