@@ -799,6 +799,11 @@ static foap4_status mlp_fail(foap4_mlp *net, foap4_status st, const std::string 
     if (e_ != hipSuccess) return mlp_fail((net), FOAP4_E_HIP, std::string(#call ": ") + hipGetErrorString(e_)); \
   } while (0)
 
+// The Adam moments, with the counting kernel's ticket right behind them: setting
+// the weights, which every evaluation needs first, clears both in one call (of a
+// multiple of 16 bytes, which is one launch).
+constexpr size_t kMomentBytes = 2 * (size_t)kMlpParams * 8;
+
 static bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
 extern "C" {
@@ -815,21 +820,20 @@ foap4_status foap4_mlp_create(void *hip_stream, foap4_mlp **out) {
     bytes += (n + 255) & ~(size_t)255;
     return at;
   };
-  const size_t w = part(kMlpParams * 4), mv = part(2 * kMlpParams * 8), res = part(sizeof(MlpResult)),
-               frag = part(kMlpFrags * 64 * 16), cls = part(4 * 4), cnt = part(kCountGrid * 4 * 8), ticket = part(4);
-  char *p = nullptr;
-  if (hipMalloc(&net->d_fixed, bytes) != hipSuccess ||
-      hipMemsetAsync((p = (char *)net->d_fixed) + ticket, 0, 4, net->stream) != hipSuccess) {
+  const size_t w = part(kMlpParams * 4), mv = part(kMomentBytes + 16), res = part(sizeof(MlpResult)),
+               frag = part(kMlpFrags * 64 * 16), cls = part(4 * 4), cnt = part(kCountGrid * 4 * 8);
+  if (hipMalloc(&net->d_fixed, bytes) != hipSuccess) {
     foap4_mlp_destroy(net);
     return mlp_fail(nullptr, FOAP4_E_HIP, "device allocation failed");
   }
+  char *p = (char *)net->d_fixed;
   net->d_w = (float *)(p + w);
   net->d_mv = (double *)(p + mv);
   net->d_res = (MlpResult *)(p + res);
   net->d_frag = p + frag;
   net->d_cls = (float *)(p + cls);
   net->d_cnt = (unsigned long long *)(p + cnt);
-  net->d_ticket = (unsigned *)(p + ticket);
+  net->d_ticket = (unsigned *)(p + mv + kMomentBytes);
   *out = net;
   return FOAP4_OK;
 }
@@ -855,7 +859,7 @@ foap4_status foap4_mlp_set_params(foap4_mlp *net, const float *w_host, int64_t n
   if (!net || !w_host) return mlp_fail(net, FOAP4_E_INVALID, "null argument");
   if (n != kMlpParams) return mlp_fail(net, FOAP4_E_INVALID, "expected FOAP4_MLP_NPARAM parameters");
   M_HIP(net, hipMemcpyAsync(net->d_w, w_host, kMlpParams * 4, hipMemcpyHostToDevice, net->stream));
-  M_HIP(net, hipMemsetAsync(net->d_mv, 0, 2 * kMlpParams * 8, net->stream));
+  M_HIP(net, hipMemsetAsync(net->d_mv, 0, kMomentBytes + 16, net->stream));  // and the counting ticket
   foap4_status st = repack(net);
   if (st != FOAP4_OK) return st;
   M_HIP(net, hipStreamSynchronize(net->stream));
