@@ -380,8 +380,9 @@ foap4_status foap4_batch_create(foap4_mesh *const *meshes, int32_t n_meshes, foa
 foap4_status foap4_batch_destroy(foap4_batch *batch);
 
 /* Work decomposition of the batched stage kernel: kslabs = 1, 2 or 4 k-slabs
- * per block tile at least (a batch that would leave compute units idle takes
- * thinner slabs; the results are identical), wg_stage1 and
+ * per block tile, of 8 planes or more (the results are identical; a batch that
+ * was never configured takes as many slabs, down to single planes, as fill the
+ * compute units), wg_stage1 and
  * wg_stage2 = workgroups per compute unit of the persistent grid of the
  * first and the second Heun stage (0: one workgroup per work item, no
  * persistence; the two stages differ in registers and traffic, so their
@@ -393,7 +394,7 @@ foap4_status foap4_batch_destroy(foap4_batch *batch);
  * neighbouring blocks instead of copying them into ghost cells first (the
  * results are identical; round R1 then runs only the SRL copies whose ghosts
  * a coarse-to-fine prolongation reads: the records with a side that is the
- * coarse block of a C2F record).  Defaults: 1, 0, 0, 1, 1.
+ * coarse block of a C2F record).  Defaults: 1 (by size, as above), 0, 0, 1, 1.
  * FOAP4_E_INVALID outside those ranges (workgroups per CU: 0 .. 64). */
 foap4_status foap4_batch_set_config(foap4_batch *batch, int32_t kslabs, int32_t wg_stage1,
                                     int32_t wg_stage2, int32_t xcd_order, int32_t gather_halos);
@@ -404,7 +405,8 @@ foap4_status foap4_batch_set_config(foap4_batch *batch, int32_t kslabs, int32_t 
  * whole step; results are cached in the JSON file cache_path (may be NULL)
  * keyed by GPU architecture, precision and the batch's block-size mix.  The
  * meshes' states are restored afterwards.  Writes the chosen {kslabs,
- * wg_stage1, wg_stage2, xcd_order} to cfg_out[4] (may be NULL). */
+ * wg_stage1, wg_stage2, xcd_order} to cfg_out[4] (may be NULL); {1, 0, 0, 1}
+ * stands for the defaults, which leave the k-slabs to the batch's size. */
 foap4_status foap4_batch_autotune(foap4_batch *batch, const char *cache_path, int32_t *cfg_out);
 /* (Phase timing and the autotuner time Heun's two stages: FOAP4_E_INVALID for
  * a batch with another integrator, whose generic sub-steps use the stage-2

@@ -29,54 +29,11 @@ foap4_status fail(foap4_mesh *m, foap4_status s, const std::string &msg) {
 // records measure faster.
 static bool srl_x_by_block(const foap4_mesh *m) { return m->d.ndim == 3 && m->d.block_n >= 16; }
 
-// Planes per work item of a MUSCL stage launch over the given meshes (3D): a
-// tile is split along z into slabs of a power of two of planes where whole
-// tiles leave CUs idle or end in a nearly empty round.  A launch of I items
-// puts n = ceil(I / CUs) on a CU; S of them run at once (by registers and
-// LDS), and a round of r <= S items takes about (r + 1.25 S) / (2.25 S) of a
-// full one, because few waves wait more on their own chains.  An item costs
-// its planes plus two (the planes around a slab are loaded and converted
-// again).  The least of rounds x planes is taken; where block sizes are mixed, of
-// the mean item's, plus what the longest exceeds it by (38,540 blocks of 8^3, 16^3
-// and 32^3: 14.1 ms a step whole*, 14.6 with 16 planes per item).  Measured, two
-// Heun steps in us by planes per item (the choice marked): FP32 180 blocks of
-// 16^3: 163 (16), 126 (8), 102 (4)*, 105 (2); 512 blocks: 190 (16), 152 (8)*, 173 (4); 720: 211
-// (16)*, 219 (8); 80 blocks of 32^3: 327 (32), 219 (16)*, 218 (8), 235 (4); one:
-// 275 (32), 52 (1)*; FP64 180 of 16^3: 204 (16), 162 (8)*, 176 (4); 27 of 32^3:
-// 204 (16), 156 (8)*, 196 (4); 512 of 8^3: FP32 96 (8), 82 (4), 85 (2)*.
-static int slab_planes(foap4_mesh *const *meshes, size_t n_meshes, int n_cu) {
-  int largest = 0, smallest = 64;
-  for (size_t i = 0; i < n_meshes; i++) {
-    largest = std::max(largest, (int)meshes[i]->d.block_n);
-    smallest = std::min(smallest, (int)meshes[i]->d.block_n);
-  }
-  const bool f64 = meshes[0]->d.prec == FOAP4_F64, mixed = smallest != largest;
-  const int at_once = f64 ? (smallest == 8 || mixed ? 1 : 2) : (smallest == 8 || mixed ? 3 : 4);
-  int best = largest;
-  double best_cost = 0.0;
-  for (int kd = largest; kd >= 1; kd /= 2) {
-    int64_t items = 0, planes = 0;
-    for (size_t i = 0; i < n_meshes; i++) {
-      const int N = meshes[i]->d.block_n;
-      const int64_t it = stage_items_for(3, N, (int64_t)meshes[i]->topo.leaves.size(), std::max(1, N / kd));
-      items += it;
-      planes += it * (std::min(N, kd) + 2);
-    }
-    const int64_t n = (items + n_cu - 1) / n_cu, full = n / at_once, rest = n % at_once;
-    const double rounds = (double)full + (rest ? (rest + 1.25 * at_once) / (2.25 * at_once) : 0.0);
-    const double mean = items ? (double)planes / items : 0.0;
-    const double cost = rounds * mean + (kd + 2 - mean);
-    if (kd == largest || cost < best_cost) {
-      best = kd;
-      best_cost = cost;
-    }
-  }
-  return best;
-}
-
 // k-slabs per tile of a mesh's own steps
-static int step_slabs(foap4_mesh *m) {
-  return m->d.ndim == 3 ? m->d.block_n / slab_planes(&m, 1, m->n_cu) : 1;
+static int step_slabs(const foap4_mesh *m) {
+  if (m->d.ndim != 3) return 1;
+  const BlockSet set{m->d.block_n, (int64_t)m->topo.leaves.size()};
+  return set.N / slab_planes(&set, 1, m->d.prec == FOAP4_F64, m->n_cu);
 }
 
 MeshDev make_dev(const foap4_mesh *m, int ks, int gather, bool x_by_block) {
@@ -228,7 +185,8 @@ struct foap4_batch {
   int nv = 5;          // variables per cell, shared by all meshes
   int max_n = 0, max_g = 0;  // largest block size and ghost width
   bool f64 = false;
-  int ks = 1, wg1 = 0, wg2 = 0, gather = 1, xcd = 1;  // wg1 / wg2: workgroups per CU of stage 1 / 2
+  int ks = 0;  // configured k-slabs per tile, 0: nothing configured, slab_planes() chooses
+  int wg1 = 0, wg2 = 0, gather = 1, xcd = 1;  // wg1 / wg2: workgroups per CU of stage 1 / 2
   MeshDev *d_devs = nullptr;
   int64_t total_items = 0, r1_total = 0, r2_total = 0;
   int nmask = 0;
@@ -526,7 +484,7 @@ foap4_status foap4_step(foap4_mesh *m, int32_t n_steps, double *t_out, double *d
   if (nsub) {
     const bool f64 = m->d.prec == FOAP4_F64;
     const int ndim = m->d.ndim;
-    const int64_t items = stage_items_for(ndim, m->d.block_n, (int64_t)m->topo.leaves.size(), step_slabs(m));
+    const int64_t items = stage_items(ndim, m->d.block_n, (int64_t)m->topo.leaves.size(), step_slabs(m));
     foap4_status st;
     if ((st = ensure_dt(m)) != FOAP4_OK) return st;
     for (int32_t s = 0; s < n_steps; s++) {
@@ -544,7 +502,7 @@ foap4_status foap4_step(foap4_mesh *m, int32_t n_steps, double *t_out, double *d
   }
   const bool f64 = m->d.prec == FOAP4_F64;
   const int ndim = m->d.ndim;
-  const int64_t items = stage_items_for(ndim, m->d.block_n, (int64_t)m->topo.leaves.size(), step_slabs(m));
+  const int64_t items = stage_items(ndim, m->d.block_n, (int64_t)m->topo.leaves.size(), step_slabs(m));
   foap4_status st;
   if ((st = ensure_dt(m)) != FOAP4_OK) return st;
   const size_t nb = m->topo.leaves.size();
@@ -831,18 +789,23 @@ static void drop_graph(foap4_batch *b) {
   b->graph_valid = false;
 }
 
+// planes per work item where no k-slabs are configured (3D)
+static int model_planes(const foap4_batch *b) {
+  std::vector<BlockSet> sets;
+  for (const foap4_mesh *m : b->meshes) sets.push_back({m->d.block_n, (int64_t)m->topo.leaves.size()});
+  return slab_planes(sets.data(), sets.size(), b->f64, b->n_cu);
+}
+
 static foap4_status batch_upload(foap4_batch *b) {
   std::vector<MeshDev> devs;
   int64_t it = 0, r1 = 0, r2 = 0;
-  // slabs as configured, or thinner ones where the batch would not fill the chip
-  const int kd = b->ndim == 3 ? slab_planes(b->meshes.data(), b->meshes.size(), b->n_cu) : 1;
+  const int planes = b->ndim == 3 && !b->ks ? model_planes(b) : 1;
   for (foap4_mesh *m : b->meshes) {
-    const int N = m->d.block_n;
-    MeshDev d = make_dev(m, b->ndim == 3 ? std::max(std::min(b->ks, N / 8), N / kd) : 1, b->gather);
+    MeshDev d = make_dev(m, b->ndim == 3 ? batch_slabs(b->ks, m->d.block_n, planes) : 1, b->gather);
     d.item_begin = it;
     d.r1_begin = r1;
     d.r2_begin = r2;
-    it += stage_items_for(b->ndim, m->d.block_n, d.nb, d.ks);
+    it += stage_items(b->ndim, m->d.block_n, d.nb, d.ks);
     r1 += d.r1_srl + m->pat.n[kF2C] + m->pat.n[kBC];
     r2 += m->pat.n[kC2F];
     devs.push_back(d);
@@ -1019,12 +982,8 @@ foap4_status foap4_batch_destroy(foap4_batch *b) {
   return FOAP4_OK;
 }
 
-foap4_status foap4_batch_set_config(foap4_batch *b, int32_t kslabs, int32_t wg_stage1, int32_t wg_stage2,
-                                    int32_t xcd_order, int32_t gather_halos) {
-  if (!b || (kslabs != 1 && kslabs != 2 && kslabs != 4) || wg_stage1 < 0 || wg_stage1 > 64 || wg_stage2 < 0 ||
-      wg_stage2 > 64 || xcd_order < 0 || xcd_order > 2 || (gather_halos != 0 && gather_halos != 1))
-    return batch_fail(b, FOAP4_E_INVALID,
-                      "kslabs must be 1, 2 or 4, 0 <= workgroups per CU <= 64, xcd_order 0, 1 or 2, gather_halos 0 or 1");
+// kslabs 0: as many as slab_planes() chooses, the state of a new batch
+static void configure(foap4_batch *b, int kslabs, int wg_stage1, int wg_stage2, int xcd_order, int gather_halos) {
   if (b->ks != kslabs || b->wg1 != wg_stage1 || b->wg2 != wg_stage2 || b->xcd != xcd_order || b->gather != gather_halos)
     drop_graph(b);
   b->ks = kslabs;
@@ -1032,6 +991,15 @@ foap4_status foap4_batch_set_config(foap4_batch *b, int32_t kslabs, int32_t wg_s
   b->wg2 = wg_stage2;
   b->xcd = xcd_order;
   b->gather = gather_halos;
+}
+
+foap4_status foap4_batch_set_config(foap4_batch *b, int32_t kslabs, int32_t wg_stage1, int32_t wg_stage2,
+                                    int32_t xcd_order, int32_t gather_halos) {
+  if (!b || (kslabs != 1 && kslabs != 2 && kslabs != 4) || wg_stage1 < 0 || wg_stage1 > 64 || wg_stage2 < 0 ||
+      wg_stage2 > 64 || xcd_order < 0 || xcd_order > 2 || (gather_halos != 0 && gather_halos != 1))
+    return batch_fail(b, FOAP4_E_INVALID,
+                      "kslabs must be 1, 2 or 4, 0 <= workgroups per CU <= 64, xcd_order 0, 1 or 2, gather_halos 0 or 1");
+  configure(b, kslabs, wg_stage1, wg_stage2, xcd_order, gather_halos);
   return FOAP4_OK;
 }
 
@@ -1053,7 +1021,7 @@ foap4_status foap4_batch_phase_times(foap4_batch *b, int32_t n_steps, double *ou
   if (!b || n_steps < 1 || !out_ms) return batch_fail(b, FOAP4_E_INVALID, "bad arguments");
   if (b->integrator != FOAP4_RK_HEUN || b->weno)
     return batch_fail(b, FOAP4_E_INVALID, "phase timing and autotuning time the Heun stages of the plane kernel");
-  if (b->adv && b->ks != 1)
+  if (b->adv && b->ks > 1)
     return batch_fail(b, FOAP4_E_INVALID, "the advection kernel has no k-slabs");
   foap4_status st = batch_prepare(b);
   if (st != FOAP4_OK) return st;
@@ -1184,13 +1152,21 @@ static void cache_store(const char *path, const std::string &key, const int cfg[
   o << "}\n";
 }
 
+// A tuned configuration; the defaults {1, 0, 0, 1} leave the slabs to slab_planes().
+static const int kDefaultCfg[4] = {1, 0, 0, 1};
+static foap4_status apply_tuned(foap4_batch *b, const int cfg[4]) {
+  foap4_status st = foap4_batch_set_config(b, cfg[0], cfg[1], cfg[2], cfg[3], b->gather);
+  if (st == FOAP4_OK && std::equal(cfg, cfg + 4, kDefaultCfg)) configure(b, 0, 0, 0, 1, b->gather);
+  return st;
+}
+
 foap4_status foap4_batch_autotune(foap4_batch *b, const char *cache_path, int32_t *cfg_out) {
   if (!b) return batch_fail(nullptr, FOAP4_E_INVALID, "null batch");
   if (b->adv) return batch_fail(b, FOAP4_E_INVALID, "the advection kernel has no launch configuration to tune");
   const std::string key = batch_key(b);
   int cached[4] = {1, 0, 0, 1};
   if (cache_lookup(cache_path, key, cached)) {
-    foap4_status st = foap4_batch_set_config(b, cached[0], cached[1], cached[2], cached[3], b->gather);
+    foap4_status st = apply_tuned(b, cached);
     if (cfg_out)
       for (int i = 0; i < 4; i++) cfg_out[i] = cached[i];
     return st;
@@ -1329,6 +1305,26 @@ foap4_status foap4_batch_autotune(foap4_batch *b, const char *cache_path, int32_
     }
     if (result == FOAP4_OK) (stage == 1 ? best_cfg[1] : best_cfg[2]) = best_wg;
   }
+  // Where the defaults split the tiles, they are no candidate above: they are
+  // compared with the choice, three runs of three steps each, by the medians
+  const bool splits = b->ndim == 3 && model_planes(b) < 8 * max_ks;
+  float whole[2] = {0.0f, 0.0f};
+  for (int c = 0; c < 2 && result == FOAP4_OK && splits; c++) {
+    if (c == 0) configure(b, best_cfg[0], best_cfg[1], best_cfg[2], best_cfg[3], b->gather);
+    else configure(b, 0, 0, 0, 1, b->gather);
+    if ((result = foap4_batch_step(b, 1)) != FOAP4_OK) break;  // warm-up
+    float t[3];
+    for (int rep = 0; rep < 3 && result == FOAP4_OK; rep++) {
+      double ph[8];
+      result = foap4_batch_phase_times(b, 3, ph);
+      t[rep] = (float)ph[5];
+    }
+    if (result != FOAP4_OK) break;
+    std::sort(t, t + 3);
+    whole[c] = t[1];
+    if (restore() != hipSuccess) { result = FOAP4_E_HIP; break; }
+  }
+  if (result == FOAP4_OK && whole[1] < whole[0]) std::copy(kDefaultCfg, kDefaultCfg + 4, best_cfg);
   const hipError_t re = restore();
   for (void *p : saved) (void)hipFree(p);
   if (result != FOAP4_OK) return result;
@@ -1336,7 +1332,7 @@ foap4_status foap4_batch_autotune(foap4_batch *b, const char *cache_path, int32_
   cache_store(cache_path, key, best_cfg);
   if (cfg_out)
     for (int i = 0; i < 4; i++) cfg_out[i] = best_cfg[i];
-  return foap4_batch_set_config(b, best_cfg[0], best_cfg[1], best_cfg[2], best_cfg[3], b->gather);
+  return apply_tuned(b, best_cfg);
 }
 
 }  // extern "C"

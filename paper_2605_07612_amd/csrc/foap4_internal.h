@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "foap4.h"
+#include "launch_rules.h"
 
 namespace f4 {
 
@@ -290,7 +291,6 @@ hipError_t launch_ghost(const MeshDev *d_meshes, int n_meshes, int64_t total, in
 hipError_t launch_srl_x_blocks(const MeshDev *d_mesh, int64_t nblocks, int which, int ndim, bool f64, hipStream_t s,
                                int nv);
 // stage.hip
-int64_t stage_items_for(int ndim, int N, int64_t nb, int ks);
 // nmask: block sizes present in the launch (1: N = 8, 2: N = 16, 4: N = 32);
 // scheme: scheme_of() of the meshes in the launch; stage 1 / 2: Heun's stages,
 // stage 3: the generic sub-step ss, stage 4: the same with three earlier states

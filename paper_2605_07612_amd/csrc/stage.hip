@@ -43,9 +43,17 @@ struct TileCfg {
   static constexpr int SUB = 256 / (TX * TY);        // sub-tiles per workgroup
   static constexpr int TPB = (N / TX) * (N / TY);    // tiles per block plane
 };
-// the host counts items without the value type: both tilings give the same
-static_assert(TileCfg<32, 3, 4>::TPB == TileCfg<32, 3, 8>::TPB && TileCfg<32, 3, 4>::SUB == TileCfg<32, 3, 8>::SUB,
-              "item counts must not depend on the value type");
+// the host counts items without the value type: stage_items() holds for every tiling
+template <int N, int NDIM, int TB>
+constexpr bool counts_match() {
+  using C = TileCfg<N, NDIM, TB>;
+  return C::SUB == stage_blocks_per_item(N) && C::TPB == stage_tiles_per_block(N);
+}
+static_assert(counts_match<8, 3, 4>() && counts_match<16, 3, 4>() && counts_match<32, 3, 4>() &&
+                  counts_match<8, 3, 8>() && counts_match<16, 3, 8>() && counts_match<32, 3, 8>() &&
+                  counts_match<8, 2, 4>() && counts_match<16, 2, 4>() && counts_match<32, 2, 4>() &&
+                  counts_match<8, 2, 8>() && counts_match<16, 2, 8>() && counts_match<32, 2, 8>(),
+              "the kernel's items are those the host counts");
 
 // Primitive planes held in LDS: k, k+1, k+2 in a ring of three slots (3D).
 template <int NDIM>
@@ -719,18 +727,6 @@ template hipError_t launch_stage_sch<F4_SCHEME>(const MeshDev *, int, int64_t, i
 template hipError_t launch_feat_sch<F4_SCHEME>(const MeshDev *, int64_t, int, bool, int, double *, hipStream_t);
 
 #if F4_SCHEME == 0
-template <int N, int NDIM>
-static int64_t items_of(int64_t nb, int ks) {
-  using C = TileCfg<N, NDIM>;
-  const int64_t tiles = nb * C::TPB;
-  return ((tiles + C::SUB - 1) / C::SUB) * (NDIM == 3 ? ks : 1);
-}
-
-int64_t stage_items_for(int ndim, int N, int64_t nb, int ks) {
-  if (ndim == 3) return N == 8 ? items_of<8, 3>(nb, ks) : N == 16 ? items_of<16, 3>(nb, ks) : items_of<32, 3>(nb, ks);
-  return N == 8 ? items_of<8, 2>(nb, ks) : N == 16 ? items_of<16, 2>(nb, ks) : items_of<32, 2>(nb, ks);
-}
-
 // the other schemes' launchers live in the other compiles of this file
 #define F4_EXTERN_SCHEME(S)                                                                                    \
   extern template hipError_t launch_stage_sch<S>(const MeshDev *, int, int64_t, int, int, bool, int,          \

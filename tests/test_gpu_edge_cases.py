@@ -257,3 +257,28 @@ def test_batch_config_rejects_bad_arguments(f4, kw):
         b.set_config(**args)
     b.step(1)
     assert m.time()[0] > 0
+
+
+def test_configured_slabs_run_and_defaults_split(f4):
+    """One 32^3 block is four tiles: as configured, whole tiles march 32 planes
+    on four compute units; a batch that was never configured splits them (52
+    against 275 us for two steps), and the autotuner keeps what is faster."""
+    from paper_2605_07612_amd import layout
+    m = f4.Mesh(3, (1, 1, 1), 32, 2, 1.0, prec=f4.F32)
+    layout.set_from_field(m, synth.two_level_blast(base_trees=1, block=32)["field"])
+
+    def stage_ms(b):
+        b.step(20)
+        return min(b.phase_times(5)["stage"] for _ in range(5))
+
+    b = f4.Batch([m])
+    unset = stage_ms(b)
+    b.set_config(kslabs=1)
+    whole = stage_ms(b)
+    b.set_config(kslabs=4)
+    four = stage_ms(b)
+    cfg = b.autotune()
+    tuned = stage_ms(b)
+    say("stage ms: never configured", unset, "whole tiles", whole, "4 slabs", four, "tuned", cfg, tuned)
+    assert whole > 2 * unset and whole > 1.5 * four
+    assert tuned < 1.5 * unset
