@@ -349,20 +349,12 @@ __global__ __launch_bounds__(MAXT) void advect_kernel(const MeshDev *__restrict_
 }
 
 template <typename T, int NDIM, int LIM>
-static void launch_adv(int64_t nb, int N, int g, const MeshDev *d, int stage, const SubStep &ss, hipStream_t s) {
+static void launch_adv(int64_t nb, int N, int g, int n_cu, const MeshDev *d, int stage, const SubStep &ss,
+                       hipStream_t s) {
   const unsigned threads = (unsigned)(N * N);
-  // A block per workgroup, or slabs of its planes (halved as long as needed)
-  // where whole blocks leave CUs without waves to hide their loads behind: up to
-  // two workgroups of 256 threads a CU, one of 64.  Two Heun steps, van Leer, us:
-  // FP32 180 blocks of 16^3 61 whole, 48; 27 of 32^3 132 and 46; 80 of 32^3 135
-  // and 86 (100 with twice as many); one of 32^3 124 and 29; 512 of 8^3 49 and
-  // 59; FP64 WENO5 80 of 32^3 462 and 248.  Its own variant, because the slab's
-  // bounds cost registers that whole blocks need (256^3 cells: 197 and 214).
-  int ls = 0;
-  if (NDIM == 3) {
-    const int64_t want = N == 8 ? 256 * 64 : 512 * 256;
-    while ((N >> ls) > 1 && ((nb * threads) << ls) < want) ls++;
-  }
+  // slabs are a variant of their own, because their bounds cost registers that
+  // whole blocks need (256^3 cells: 197 and 214 us)
+  const int ls = NDIM == 3 ? advect_log2_slabs(nb, N, n_cu) : 0;
   const unsigned grid = (unsigned)(nb << ls);
   const size_t lds = (size_t)adv_lds(N, g) * sizeof(T);
 #define F4_ADV(STG, MAXT, HS)                                                                                 \
@@ -393,23 +385,23 @@ static void launch_adv(int64_t nb, int N, int g, const MeshDev *d, int stage, co
 }
 
 template <typename T, int NDIM>
-static void launch_adv_limiter(int64_t nb, int N, int g, const MeshDev *d, int stage, int limiter, const SubStep &ss,
-                               hipStream_t s) {
-  if (limiter == FOAP4_LIM_WENO5) launch_adv<T, NDIM, 2>(nb, N, g, d, stage, ss, s);
-  else if (limiter == FOAP4_LIM_VANLEER) launch_adv<T, NDIM, 1>(nb, N, g, d, stage, ss, s);
-  else launch_adv<T, NDIM, 0>(nb, N, g, d, stage, ss, s);
+static void launch_adv_limiter(int64_t nb, int N, int g, int n_cu, const MeshDev *d, int stage, int limiter,
+                               const SubStep &ss, hipStream_t s) {
+  if (limiter == FOAP4_LIM_WENO5) launch_adv<T, NDIM, 2>(nb, N, g, n_cu, d, stage, ss, s);
+  else if (limiter == FOAP4_LIM_VANLEER) launch_adv<T, NDIM, 1>(nb, N, g, n_cu, d, stage, ss, s);
+  else launch_adv<T, NDIM, 0>(nb, N, g, n_cu, d, stage, ss, s);
 }
 
-hipError_t launch_advect_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int n_ghost, int stage, int ndim,
-                               bool f64, int limiter, hipStream_t s, const SubStep &ss) {
+hipError_t launch_advect_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int n_ghost, int n_cu, int stage,
+                               int ndim, bool f64, int limiter, hipStream_t s, const SubStep &ss) {
   if (nblocks <= 0) return hipSuccess;
   const int64_t nb = nblocks;
   if (f64) {
-    if (ndim == 3) launch_adv_limiter<double, 3>(nb, block_n, n_ghost, d_mesh, stage, limiter, ss, s);
-    else launch_adv_limiter<double, 2>(nb, block_n, n_ghost, d_mesh, stage, limiter, ss, s);
+    if (ndim == 3) launch_adv_limiter<double, 3>(nb, block_n, n_ghost, n_cu, d_mesh, stage, limiter, ss, s);
+    else launch_adv_limiter<double, 2>(nb, block_n, n_ghost, n_cu, d_mesh, stage, limiter, ss, s);
   } else {
-    if (ndim == 3) launch_adv_limiter<float, 3>(nb, block_n, n_ghost, d_mesh, stage, limiter, ss, s);
-    else launch_adv_limiter<float, 2>(nb, block_n, n_ghost, d_mesh, stage, limiter, ss, s);
+    if (ndim == 3) launch_adv_limiter<float, 3>(nb, block_n, n_ghost, n_cu, d_mesh, stage, limiter, ss, s);
+    else launch_adv_limiter<float, 2>(nb, block_n, n_ghost, n_cu, d_mesh, stage, limiter, ss, s);
   }
   return hipGetLastError();
 }

@@ -141,9 +141,9 @@ static foap4_status fill(foap4_mesh *m, const MeshDev *dd, int which) {
   const int64_t r1 = m->pat.n[kSRL] - nx + m->pat.n[kF2C] + m->pat.n[kBC], r2 = m->pat.n[kC2F];
   if (nx) F4_HIP(m, launch_srl_x_blocks(dd, (int64_t)m->topo.leaves.size(), which, m->d.ndim, f64, m->stream,
                                         m->nvar));
-  F4_HIP(m, launch_ghost(dd, 1, r1, 1, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->stream,
+  F4_HIP(m, launch_ghost(dd, 1, r1, 1, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->n_cu, m->stream,
                          m->nvar));
-  if (r2) F4_HIP(m, launch_ghost(dd, 1, r2, 2, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->stream,
+  if (r2) F4_HIP(m, launch_ghost(dd, 1, r2, 2, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->n_cu, m->stream,
                          m->nvar));
   return FOAP4_OK;
 }
@@ -158,9 +158,9 @@ static foap4_status fill(foap4_mesh *m, const MeshDev *dd, int which) {
 static foap4_status fill_step(foap4_mesh *m, int which) {
   const bool f64 = m->d.prec == FOAP4_F64;
   const int64_t r1 = (int64_t)m->pat.n_srl_c2f + m->pat.n[kF2C] + m->pat.n[kBC], r2 = m->pat.n[kC2F];
-  F4_HIP(m, launch_ghost(m->d_dev + 1, 1, r1, 1, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->stream,
+  F4_HIP(m, launch_ghost(m->d_dev + 1, 1, r1, 1, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->n_cu, m->stream,
                          m->nvar));
-  F4_HIP(m, launch_ghost(m->d_dev + 1, 1, r2, 2, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->stream,
+  F4_HIP(m, launch_ghost(m->d_dev + 1, 1, r2, 2, which, m->d.ndim, f64, m->d.block_n, m->d.n_ghost, m->n_cu, m->stream,
                          m->nvar));
   return FOAP4_OK;
 }
@@ -462,11 +462,11 @@ static hipError_t mesh_stage(foap4_mesh *m, int64_t items, int stage, const SubS
   const bool f64 = m->d.prec == FOAP4_F64;
   const int ndim = m->d.ndim;
   if (m->d.physics == FOAP4_PHYS_ADVECTION)
-    return launch_advect_stage(m->d_dev + 1, (int64_t)m->topo.leaves.size(), m->d.block_n, m->d.n_ghost, stage, ndim, f64,
-                               m->d.limiter, m->stream, ss);
+    return launch_advect_stage(m->d_dev + 1, (int64_t)m->topo.leaves.size(), m->d.block_n, m->d.n_ghost, m->n_cu, stage,
+                               ndim, f64, m->d.limiter, m->stream, ss);
   if (m->d.limiter == FOAP4_LIM_WENO5) {
-    return launch_weno_stage(m->d_dev + 1, (int64_t)m->topo.leaves.size(), m->d.block_n, stage, ndim, f64, scheme_of(m->d),
-                             m->stream, ss);
+    return launch_weno_stage(m->d_dev + 1, (int64_t)m->topo.leaves.size(), m->d.block_n, m->n_cu, stage, ndim, f64,
+                             scheme_of(m->d), m->stream, ss);
   }
   return launch_stage(m->d_dev + 1, 1, items, stage, ndim, f64, 0, m->stream, item_order(1, stage, &m, 1),
                       nmask_of(m->d.block_n), scheme_of(m->d),
@@ -836,7 +836,7 @@ static hipError_t batch_stage(foap4_batch *b, int stage, int grid, hipStream_t s
     for (int i = 0; i < n; i++) {
       const foap4_mesh *m = b->meshes[i];
       hipError_t e = launch_advect_stage(b->d_devs + i, (int64_t)m->topo.leaves.size(), m->d.block_n, m->d.n_ghost,
-                                         stage, b->ndim, b->f64, m->d.limiter, s, ss);
+                                         b->n_cu, stage, b->ndim, b->f64, m->d.limiter, s, ss);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -846,8 +846,8 @@ static hipError_t batch_stage(foap4_batch *b, int stage, int grid, hipStream_t s
                         item_order(b->xcd, stage, b->meshes.data(), b->meshes.size()), b->nmask, b->scheme, ss);
   for (int i = 0; i < n; i++) {
     const foap4_mesh *m = b->meshes[i];
-    hipError_t e = launch_weno_stage(b->d_devs + i, (int64_t)m->topo.leaves.size(), m->d.block_n, stage, b->ndim,
-                                     b->f64, b->scheme, s, ss);
+    hipError_t e = launch_weno_stage(b->d_devs + i, (int64_t)m->topo.leaves.size(), m->d.block_n, b->n_cu, stage,
+                                     b->ndim, b->f64, b->scheme, s, ss);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -860,8 +860,8 @@ static hipError_t batch_enqueue_step(foap4_batch *b, hipStream_t s) {
   const int nsub = substeps_of(b->integrator, &subs);
   for (int k = 0; k < nsub; k++) {  // integrators with extra states: generic sub-steps
     const int which = subs[k].deriv;
-    if ((e = launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv)) != hipSuccess) return e;
-    if (b->r2_total && (e = launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv)) != hipSuccess)
+    if ((e = launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, b->max_n, b->max_g, b->n_cu, s, b->nv)) != hipSuccess) return e;
+    if (b->r2_total && (e = launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, b->max_n, b->max_g, b->n_cu, s, b->nv)) != hipSuccess)
       return e;
     const int form = substep_form(subs[k]);
     if ((e = batch_stage(b, form, stage_grid(b, 2), s, subs[k])) != hipSuccess) return e;
@@ -875,8 +875,8 @@ static hipError_t batch_enqueue_step(foap4_batch *b, hipStream_t s) {
   for (int stage = 1; stage <= 2; stage++) {
     const int which = stage - 1;
     const int grid = stage_grid(b, stage);
-    if ((e = launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv)) != hipSuccess) return e;
-    if (b->r2_total && (e = launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv)) != hipSuccess)
+    if ((e = launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, b->max_n, b->max_g, b->n_cu, s, b->nv)) != hipSuccess) return e;
+    if (b->r2_total && (e = launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, b->max_n, b->max_g, b->n_cu, s, b->nv)) != hipSuccess)
       return e;
     if ((e = batch_stage(b, stage, grid, s)) != hipSuccess) return e;
     for (int i = 0; i < n; i++)
@@ -1036,9 +1036,9 @@ foap4_status foap4_batch_phase_times(foap4_batch *b, int32_t n_steps, double *ou
   for (int it = 0; it < n_steps; it++) {
     for (int stage = 1; stage <= 2; stage++) {
       const int which = stage - 1;
-      B_HIP(b, launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv));
+      B_HIP(b, launch_ghost(b->d_devs, n, b->r1_total, 1, which, b->ndim, b->f64, b->max_n, b->max_g, b->n_cu, s, b->nv));
       B_HIP(b, hipEventRecord(ev[++k], s));
-      if (b->r2_total) B_HIP(b, launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, b->max_n, b->max_g, s, b->nv));
+      if (b->r2_total) B_HIP(b, launch_ghost(b->d_devs, n, b->r2_total, 2, which, b->ndim, b->f64, b->max_n, b->max_g, b->n_cu, s, b->nv));
       B_HIP(b, hipEventRecord(ev[++k], s));
       B_HIP(b, batch_stage(b, stage, stage_grid(b, stage), s));
       B_HIP(b, hipEventRecord(ev[++k], s));

@@ -281,9 +281,9 @@ foap4_status build_pattern(foap4_mesh *m);
 // ghost.hip: round 1 = SRL + F2C + boundary, round 2 = C2F; which = state role
 // (0 current, 1 other, 2 third)
 // nv: variables per cell (ndim + 2 for the Euler system, 1 for scalar advection);
-// block_n, n_ghost: the largest of the meshes'
+// block_n, n_ghost: the largest of the meshes'; n_cu: the device's compute units
 hipError_t launch_ghost(const MeshDev *d_meshes, int n_meshes, int64_t total, int round, int which,
-                        int ndim, bool f64, int block_n, int n_ghost, hipStream_t s, int nv);
+                        int ndim, bool f64, int block_n, int n_ghost, int n_cu, hipStream_t s, int nv);
 // Same-level x faces of a single 3D mesh with stored ghosts, by block: block
 // b's first g columns into its -x neighbour's +x ghosts, its last g columns
 // into its +x neighbour's -x ghosts (the x-face SRL records, done by block).
@@ -299,11 +299,11 @@ hipError_t launch_stage(const MeshDev *d_meshes, int n_meshes, int64_t total_ite
                         int ndim, bool f64, int grid, hipStream_t s, int xcd, int nmask, int scheme,
                         const SubStep &ss = SubStep{});
 // weno.hip: the WENO5 stage (one workgroup per tile and k-slab)
-hipError_t launch_weno_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int stage, int ndim, bool f64,
-                             int scheme, hipStream_t s, const SubStep &ss = SubStep{});
+hipError_t launch_weno_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int n_cu, int stage, int ndim,
+                             bool f64, int scheme, hipStream_t s, const SubStep &ss = SubStep{});
 // advect.hip: the scalar advection stage (a workgroup per block or slab of planes)
-hipError_t launch_advect_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int n_ghost, int stage, int ndim,
-                               bool f64, int limiter, hipStream_t s, const SubStep &ss = SubStep{});
+hipError_t launch_advect_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int n_ghost, int n_cu, int stage,
+                               int ndim, bool f64, int limiter, hipStream_t s, const SubStep &ss = SubStep{});
 // stage 1 of one mesh that also reduces the raw features of its input state
 // (feat_raw [nb][2], zeroed by the caller) by atomic maxima
 hipError_t launch_stage1_features(const MeshDev *d_mesh, int64_t total_items, int ndim, bool f64, int nmask,

@@ -9,8 +9,6 @@
 // Work items of several meshes are concatenated (r1_begin / r2_begin).
 // NV, the number of variables per cell, is a template parameter: ndim + 2
 // for the Euler system, 1 for scalar advection.
-#include <algorithm>
-
 #include "foap4_internal.h"
 
 namespace f4 {
@@ -664,20 +662,15 @@ hipError_t launch_srl_x_blocks(const MeshDev *d_mesh, int64_t nblocks, int which
 }
 
 hipError_t launch_ghost(const MeshDev *d_meshes, int n_meshes, int64_t total, int round, int which,
-                        int ndim, bool f64, int block_n, int n_ghost, hipStream_t s, int nv) {
+                        int ndim, bool f64, int block_n, int n_ghost, int n_cu, hipStream_t s, int nv) {
   if (total <= 0) return hipSuccess;
-  // A record's elements take several rounds of one workgroup (an FP64 16^3
-  // prolongation: ten), each as long as a load from memory.  Launches of few
-  // records take more workgroups per record, up to eight per CU in all.  The
-  // walls of 225 16^2 columns (450 records): 14.6 us with one workgroup each,
-  // 11.7 us; what is left is the launch and four dependent loads.
   const int64_t face = (int64_t)nv * n_ghost * (ndim == 3 ? block_n * block_n : block_n);
-  const int64_t split = std::max<int64_t>(1, std::min<int64_t>((face + 511) / 512, 2048 / total));
+  const int split = ghost_split(total, face, n_cu);
   const unsigned nblk = (unsigned)(total * split);
 #define F4_GHOST(T, D, V)                                                                                     \
   do {                                                                                                        \
-    if (round == 1) ghost_kernel<T, D, V, 1><<<nblk, 256, 0, s>>>(d_meshes, n_meshes, total, (int)split, which); \
-    else ghost_kernel<T, D, V, 2><<<nblk, 256, 0, s>>>(d_meshes, n_meshes, total, (int)split, which);         \
+    if (round == 1) ghost_kernel<T, D, V, 1><<<nblk, 256, 0, s>>>(d_meshes, n_meshes, total, split, which); \
+    else ghost_kernel<T, D, V, 2><<<nblk, 256, 0, s>>>(d_meshes, n_meshes, total, split, which);         \
   } while (0)
   if (nv == 1) {  // scalar advection
     if (f64) {

@@ -73,4 +73,44 @@ inline int batch_slabs(int configured, int N, int planes) {
   return configured > 0 ? std::min(configured, N / 8) : std::max(1, N / planes);
 }
 
+// Planes per workgroup of a WENO5 stage launch (3D): a tile's whole depth, or
+// slabs of it (halved as long as needed) where whole tiles leave CUs without
+// work.  A slab converts six more planes of its columns and reconstructs two
+// more cells of each.  The line lies at three workgroups of 256 threads a CU,
+// where a second one no longer pays, and at four of one wave: 80 blocks of 32^3
+// (320 tiles), FP32, 256 CUs, two Heun steps: 701 us whole, 404 us in 4 slabs,
+// 464 us in 16; 512 blocks of 16^3: 381, 322 (2 slabs), 374 us (8); 512 of 8^3:
+// 156, 107 (2), 135 us (8); one 32^3 block: 527 and 54 us (32 slabs).
+inline int weno_planes(int64_t nblocks, int N, int n_cu) {
+  const int ts = N == 8 ? 8 : 16;
+  const int64_t tiles = nblocks * (N / ts) * (N / ts), fill = (ts == 8 ? 4 : 3) * (int64_t)n_cu;
+  int kd = N;
+  while (kd > 1 && tiles * (N / kd) < fill) kd /= 2;
+  return kd;
+}
+
+// log2 of the slabs per block of a scalar advection launch (3D): a block per
+// workgroup, or slabs of its planes (halved as long as needed) where whole
+// blocks leave CUs without waves to hide their loads behind: up to two
+// workgroups of 256 threads a CU, one of 64.  256 CUs, two Heun steps, van Leer,
+// us: FP32 180 blocks of 16^3 61 whole, 48; 27 of 32^3 132 and 46; 80 of 32^3
+// 135 and 86 (100 with twice as many); one of 32^3 124 and 29; 512 of 8^3 49 and
+// 59; FP64 WENO5 80 of 32^3 462 and 248.
+inline int advect_log2_slabs(int64_t nblocks, int N, int n_cu) {
+  const int64_t threads = N * N, want = (N == 8 ? 64 : 512) * (int64_t)n_cu;
+  int ls = 0;
+  while ((N >> ls) > 1 && ((nblocks * threads) << ls) < want) ls++;
+  return ls;
+}
+
+// Workgroups per record of a ghost round: a record's elements take several
+// rounds of one workgroup (an FP64 16^3 prolongation: ten), each as long as a
+// load from memory.  Launches of few records take more workgroups per record, up
+// to eight per CU in all.  The walls of 225 16^2 columns (450 records): 14.6 us
+// with one workgroup each, 11.7 us; what is left is the launch and four
+// dependent loads.
+inline int ghost_split(int64_t records, int64_t face_values, int n_cu) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>((face_values + 511) / 512, 8 * (int64_t)n_cu / records));
+}
+
 }  // namespace f4

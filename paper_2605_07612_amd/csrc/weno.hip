@@ -475,22 +475,12 @@ static void launch_tiles(unsigned n, int kd, const MeshDev *d, int stage, const 
 }
 
 template <typename T, int NDIM, int SCH>
-static void launch_sizes(int64_t nblocks, int N, const MeshDev *d, int stage, const SubStep &ss, hipStream_t s) {
+static void launch_sizes(int64_t nblocks, int N, int n_cu, const MeshDev *d, int stage, const SubStep &ss,
+                         hipStream_t s) {
   const int ts = N == 8 ? 8 : 16;
   const int64_t tiles = nblocks * (N / ts) * (N / ts);
-  // Planes per workgroup: a tile's whole depth, or slabs of it (halved as long
-  // as needed) where whole tiles leave CUs without work.  A slab converts six
-  // more planes of its columns and reconstructs two more cells of each.  The
-  // line lies at three workgroups of 256 threads a CU, where a second one no
-  // longer pays, and at 1024 of one wave: 80 blocks of 32^3 (320 tiles), FP32,
-  // two Heun steps: 701 us whole, 404 us in 4 slabs, 464 us in 16; 512 blocks of
-  // 16^3: 381, 322 (2 slabs), 374 us (8); 512 of 8^3: 156, 107 (2), 135 us (8);
-  // one 32^3 block: 527 and 54 us (32 slabs).
-  const int64_t fill = ts == 8 ? 1024 : 768;
-  int kd = N;
-  if (NDIM == 3)
-    while (kd > 1 && tiles * (N / kd) < fill) kd /= 2;
-  const unsigned n = (unsigned)(tiles * (NDIM == 3 ? N / kd : 1));
+  const int kd = NDIM == 3 ? weno_planes(nblocks, N, n_cu) : N;
+  const unsigned n = (unsigned)(tiles * (N / kd));
   if (ts == 8) launch_tiles<T, NDIM, 8, SCH>(n, kd, d, stage, ss, s);
   else launch_tiles<T, NDIM, 16, SCH>(n, kd, d, stage, ss, s);
 }
@@ -502,37 +492,37 @@ static void launch_sizes(int64_t nblocks, int N, const MeshDev *d, int stage, co
 #endif
 
 template <int SCH>
-hipError_t launch_weno_sch(const MeshDev *d, int64_t nblocks, int N, int stage, int ndim, bool f64, hipStream_t s,
-                           const SubStep &ss) {
+hipError_t launch_weno_sch(const MeshDev *d, int64_t nblocks, int N, int n_cu, int stage, int ndim, bool f64,
+                           hipStream_t s, const SubStep &ss) {
   if (f64) {
-    if (ndim == 3) launch_sizes<double, 3, SCH>(nblocks, N, d, stage, ss, s);
-    else launch_sizes<double, 2, SCH>(nblocks, N, d, stage, ss, s);
+    if (ndim == 3) launch_sizes<double, 3, SCH>(nblocks, N, n_cu, d, stage, ss, s);
+    else launch_sizes<double, 2, SCH>(nblocks, N, n_cu, d, stage, ss, s);
   } else {
-    if (ndim == 3) launch_sizes<float, 3, SCH>(nblocks, N, d, stage, ss, s);
-    else launch_sizes<float, 2, SCH>(nblocks, N, d, stage, ss, s);
+    if (ndim == 3) launch_sizes<float, 3, SCH>(nblocks, N, n_cu, d, stage, ss, s);
+    else launch_sizes<float, 2, SCH>(nblocks, N, n_cu, d, stage, ss, s);
   }
   return hipGetLastError();
 }
-template hipError_t launch_weno_sch<F4_SCHEME>(const MeshDev *, int64_t, int, int, int, bool, hipStream_t,
+template hipError_t launch_weno_sch<F4_SCHEME>(const MeshDev *, int64_t, int, int, int, int, bool, hipStream_t,
                                                const SubStep &);
 
 #if F4_SCHEME == 0
 #define F4_EXTERN_SCHEME(S) \
-  extern template hipError_t launch_weno_sch<S>(const MeshDev *, int64_t, int, int, int, bool, hipStream_t, \
+  extern template hipError_t launch_weno_sch<S>(const MeshDev *, int64_t, int, int, int, int, bool, hipStream_t, \
                                                 const SubStep &);
 F4_EXTERN_SCHEME(2)
 F4_EXTERN_SCHEME(4)
 F4_EXTERN_SCHEME(6)
 #undef F4_EXTERN_SCHEME
 
-hipError_t launch_weno_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int stage, int ndim, bool f64,
-                             int scheme, hipStream_t s, const SubStep &ss) {
+hipError_t launch_weno_stage(const MeshDev *d_mesh, int64_t nblocks, int block_n, int n_cu, int stage, int ndim,
+                             bool f64, int scheme, hipStream_t s, const SubStep &ss) {
   if (nblocks <= 0) return hipSuccess;
   switch (scheme & (kSchHLL | kSchGravity)) {
-    case 0: return launch_weno_sch<0>(d_mesh, nblocks, block_n, stage, ndim, f64, s, ss);
-    case kSchHLL: return launch_weno_sch<kSchHLL>(d_mesh, nblocks, block_n, stage, ndim, f64, s, ss);
-    case kSchGravity: return launch_weno_sch<kSchGravity>(d_mesh, nblocks, block_n, stage, ndim, f64, s, ss);
-    default: return launch_weno_sch<kSchHLL | kSchGravity>(d_mesh, nblocks, block_n, stage, ndim, f64, s, ss);
+    case 0: return launch_weno_sch<0>(d_mesh, nblocks, block_n, n_cu, stage, ndim, f64, s, ss);
+    case kSchHLL: return launch_weno_sch<kSchHLL>(d_mesh, nblocks, block_n, n_cu, stage, ndim, f64, s, ss);
+    case kSchGravity: return launch_weno_sch<kSchGravity>(d_mesh, nblocks, block_n, n_cu, stage, ndim, f64, s, ss);
+    default: return launch_weno_sch<kSchHLL | kSchGravity>(d_mesh, nblocks, block_n, n_cu, stage, ndim, f64, s, ss);
   }
 }
 #endif

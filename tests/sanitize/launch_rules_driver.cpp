@@ -4,6 +4,9 @@
 //
 //   planes f64 n_cu n_sets {N blocks} ...   planes per stage work item
 //   slabs configured N planes               k-slabs per tile in a batch
+//   weno blocks N n_cu                      planes per WENO5 workgroup
+//   advect blocks N n_cu                    log2 of an advection block's slabs
+//   ghost records face_values n_cu          workgroups per ghost record
 #include <cstdio>
 #include <cstring>
 #include <vector>
@@ -28,7 +31,13 @@ int main() {
       if (std::scanf("%d %d %d", &c, &N, &p) != 3) return 2;
       std::printf("%d\n", f4::batch_slabs(c, N, p));
     } else {
-      return 3;
+      long a, b;
+      int cu;
+      if (std::scanf("%ld %ld %d", &a, &b, &cu) != 3) return 2;
+      if (!std::strcmp(what, "weno")) std::printf("%d\n", f4::weno_planes(a, (int)b, cu));
+      else if (!std::strcmp(what, "advect")) std::printf("%d\n", f4::advect_log2_slabs(a, (int)b, cu));
+      else if (!std::strcmp(what, "ghost")) std::printf("%d\n", f4::ghost_split(a, b, cu));
+      else return 3;
     }
   }
   return 0;

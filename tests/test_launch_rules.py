@@ -46,3 +46,19 @@ def test_model_planes(ask):
              (1, 32, 27, 8), (0, 8, 512, 2), (0, 16, 4096, 16), (1, 16, 4096, 16), (0, 32, 512, 32)]
     assert ask(*[("planes", f64, 256, 1, N, nb) for f64, N, nb, _ in swept]) == [x[3] for x in swept]
     assert ask(("planes", 0, 256, 3, 8, 19270, 16, 6937, 32, 12333)) == [32]
+
+
+def test_rules_follow_the_compute_units(ask):
+    """Every rule fills the device it runs on: the block counts that were swept
+    on 256 CUs take the measured split there, and a device of a fourth of the
+    CUs splits a fourth of the blocks or records alike, so that it does not pay
+    for slabs that it cannot run at once."""
+    swept = [("weno", 80, 32, 8), ("weno", 512, 16, 8), ("weno", 512, 8, 4), ("weno", 4, 32, 1),
+             ("advect", 180, 16, 2), ("advect", 512, 8, 0), ("advect", 80, 32, 1), ("advect", 28, 32, 3),
+             ("ghost", 448, 5 * 2 * 256, 4), ("ghost", 4096, 5 * 2 * 256, 1), ("ghost", 4, 5 * 2 * 256, 5)]
+    assert ask(*[(w, n, x, 256) for w, n, x, _ in swept]) == [e for _, _, _, e in swept]
+    assert ask(*[(w, n // 4, x, 64) for w, n, x, _ in swept]) == [e for _, _, _, e in swept]
+    many = [("planes", p, cu, 1, N, cu // 64 * nb) for p in (0, 1) for N in (8, 16, 32) for nb in (3, 45, 128, 700)
+            for cu in (256, 64)]
+    got = ask(*many)
+    assert got[::2] == got[1::2]
