@@ -216,8 +216,10 @@ foap4_status foap4_compute_dt(foap4_mesh *mesh);
  * default; SSP-RK3 or SSP-RK(4,3), Sec. 3.1) on the current state: per
  * sub-step the ghost cells that the stage reads (the restrictions,
  * prolongations and boundary faces; same-level halos come straight from the
- * neighbouring blocks), the fused flux/update stage, and the flux fix at refinement boundaries (Sec. 2.7); the next dt comes from the new state (FP64
- * reduction on the device).  The result is in the current state buffer.
+ * neighbouring blocks), the fused flux/update stage, and the flux fix at
+ * refinement boundaries (Sec. 2.7); the next dt comes from the new state (FP64
+ * reduction on the device; for FP64 states the value that foap4_compute_dt
+ * gives).  The result is in the current state buffer.
  * FOAP4_E_ORDER if the integrator needs extra state buffers that are not set;
  * FOAP4_E_INVALID if feature capture is on with an integrator other than
  * Heun.  Enqueues only; if t_out/dt_out are non-NULL

@@ -442,7 +442,11 @@ foap4_status foap4_mesh_set_extra_state(foap4_mesh *m, int32_t index, void *stat
 // 176^3 (109 MB) 179 and 175, 160^3 (82 MB) 126 and 125; FP64 256^3 1055 and 1037,
 // 160^3 (164 MB) 268 and 264, 128^3 (84 MB) 142 and 142; below, a two-level mesh
 // of 70 MB loses 0.8 %.  Not for mixed block sizes, whose last items set the tail:
-// a batch of 8.8 GB 14.14 and 14.25 ms, one of 70 MB 0.5 % slower.
+// a batch of 8.8 GB 14.14 and 14.25 ms, one of 70 MB 0.5 % slower.  The other
+// integrators' sub-steps run first to last: with every second one turned round
+// a step of 256^3 FP32 cells takes 786 and 777 us (SSP-RK3), 1018 and 1002
+// (SSP-RK(4,3)), 1303 and 1290 (RK4), but 192^3 359 and 363 (SSP-RK3); no rule
+// for them has been drawn from that.
 static int item_order(int order, int stage, foap4_mesh *const *meshes, size_t n_meshes) {
   if (stage != 2) return order;
   int64_t bytes = 0;

@@ -449,8 +449,9 @@ __device__ __forceinline__ void stage_item(const MeshDev &M, int stage, int64_t 
       // 3D tiles of 16 x 16: the edge faces of planes k and k + 1 together,
       // every other plane, in the 64 lanes of one wave (one plane's 2 TILE
       // edge faces would leave half of it idle); the fluxes of plane k + 1
-      // wait in XE and are put in place on the next plane (the planes of a
-      // slab come in pairs: N / kslabs is even).  For 8^3 blocks each wave
+      // wait in XE and are put in place on the next plane (a slab of a single
+      // plane, or the last of an odd number, has no partner: its second half
+      // wave idles).  For 8^3 blocks each wave
       // keeps its own plane's 16 edge faces: pairing them there costs more
       // registers (and occupancy) than it saves.  A 32 x 8 tile has 40 edge
       // faces a plane, too many to pair in 64 lanes: one wave takes them on

@@ -23,9 +23,9 @@
 // loads of the next plane are issued after the reconstructions, which leaves
 // FP32 16 x 16 tiles at 114-127 registers, four waves per SIMD, no spills.
 // 160 x 160 x 192 cells in 16^3 blocks, FP32, walls and gravity, two Heun steps:
-// 1832 us with per-face reconstruction and stored ghosts (1510 us of it in the
-// stages), 779 us now; 768^2 cells in 32^2 blocks, FP64, HLL, two SSP-RK3 steps:
-// 396 us with every face evaluated by both of its cells, 195 us now.
+// 1840 us with per-face reconstruction and stored ghosts (1510 us of it in the
+// stages), 765 us now; 768^2 cells in 32^2 blocks, FP64, HLL, two SSP-RK3 steps:
+// 397 us with every face evaluated by both of its cells, 184 us now.
 #include "device_common.h"
 #include "foap4_internal.h"
 #include "stage_common.h"
@@ -34,7 +34,9 @@ namespace f4 {
 
 // FP32: the squared reciprocals of three positive values; FP64: the same
 // weights times the product of the three squares (their ratios are all that
-// counts), which needs no reciprocal and stays finite for values below 1e77.
+// counts), which needs no reciprocal.  With the differences that they multiply
+// the products stay finite for values below about 1e68, which are differences
+// of neighbouring cells of about 1e34.
 __device__ __forceinline__ void weno_weights(const float *b, float *R) {
 #pragma unroll
   for (int k = 0; k < 3; k++) {
@@ -85,10 +87,12 @@ __device__ __forceinline__ void pin(T &a) {
   asm volatile("" : "+v"(a)::"memory");
 }
 
-// Tile shape of a block size, and LDS layout.  Rows of the staged plane are
+// Tile shape of a block size, and LDS layout.  FP32 rows of the staged plane are
 // LP = 24 values apart: 24 = -8 mod 32 banks, so the half waves of an 8 x 8
 // tile (four adjacent rows) and of a 16 x 16 tile (rows r and r + 2, see the
-// lane map) touch every bank once.
+// lane map) touch every bank once.  FP64 rows are tight (TS + 6 and TS + 1
+// values), so that four 2D workgroups share a CU (34 kB each; 43 kB at 24 values
+// a row, three): 194 -> 182 us for the 2D case above.
 template <typename T, int TS>
 struct WenoTile {
   static constexpr int Q = TS + 6;                           // plane rows -3 .. TS + 2
