@@ -439,8 +439,8 @@ foap4_status foap4_mesh_set_extra_state(foap4_mesh *m, int32_t index, void *stat
 // that it starts on what the first stage read and wrote last.  By the interior
 // of one state: from 96 MiB on.  Two stages, us, first to last and last to first:
 // FP32 256^3 cells in 16^3 blocks (336 MB) 496 and 485, 192^3 (142 MB) 223 and 215,
-// 176^3 (109 MB) 179 and 175, 160^3 (82 MB) 126 and 125; FP64 256^3 1055 and 1037,
-// 160^3 (164 MB) 268 and 264, 128^3 (84 MB) 142 and 142; below, a two-level mesh
+// 176^3 (109 MB) 179 and 175, 160^3 (82 MB) 126 and 125; FP64 256^3 1069 and 1058,
+// 160^3 (164 MB) 282 and 279, 128^3 (84 MB) 150 and 150; below, a two-level mesh
 // of 70 MB loses 0.8 %.  Not for mixed block sizes, whose last items set the tail:
 // a batch of 8.8 GB 14.14 and 14.25 ms, one of 70 MB 0.5 % slower.  The other
 // integrators' sub-steps run first to last: with every second one turned round

@@ -592,8 +592,8 @@ __device__ __forceinline__ int64_t item_of(int64_t w, int64_t it, int64_t grid, 
 // FP32 kernel 3 (its LDS allows 3 workgroups per CU; at 168 registers it
 // spills a little and ran ~14 % faster than at 2 waves); FP64 kernels keep
 // what their registers allow, but RK4's last sub-step on 16^3 and 32^3 blocks,
-// at 261 registers and one wave, is held to the 2 waves that its LDS allows
-// (256^3 cells, two RK4 steps: minmod 5170 -> 4810 us, van Leer 5994 -> 5512;
+// at 265 registers and one wave, is held to the 2 waves that its LDS allows
+// (256^3 cells, two RK4 steps: minmod 5526 -> 5005 us, van Leer 6240 -> 5613;
 // given to the other sub-steps as well, the hint costs their schedule 2-4 %).
 template <typename T, int NM, int STG = 2>
 constexpr int stage_waves() {
