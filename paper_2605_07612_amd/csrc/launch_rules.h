@@ -33,10 +33,11 @@ inline int64_t stage_items(int ndim, int N, int64_t nb, int ks) {
 // the mean item's, plus what the longest exceeds it by (38,540 blocks of 8^3, 16^3
 // and 32^3: 14.1 ms a step whole*, 14.6 with 16 planes per item).  Measured, two
 // Heun steps in us by planes per item (the choice marked): FP32 180 blocks of
-// 16^3: 163 (16), 126 (8), 102 (4)*, 105 (2); 512 blocks: 190 (16), 152 (8)*, 173 (4); 720: 211
-// (16)*, 219 (8); 80 blocks of 32^3: 327 (32), 219 (16)*, 218 (8), 235 (4); one:
-// 275 (32), 52 (1)*; FP64 180 of 16^3: 210 (16), 176 (8)*, 188 (4); 27 of 32^3:
-// 212 (16), 176 (8)*, 208 (4); 512 of 8^3: 136 (8), 95 (4)*, 127 (2); 512 of 8^3: FP32 96 (8), 82 (4), 85 (2)*.
+// 16^3: 163 (16), 126 (8), 102 (4)*, 105 (2); 512: 190 (16), 152 (8)*, 173 (4);
+// 720: 211 (16)*, 219 (8); 80 blocks of 32^3: 327 (32), 219 (16)*, 218 (8),
+// 235 (4); one: 275 (32), 52 (1)*; 512 of 8^3: 96 (8), 82 (4), 85 (2)*; FP64 180
+// of 16^3: 210 (16), 176 (8)*, 188 (4); 27 of 32^3: 212 (16), 176 (8)*, 208 (4);
+// 512 of 8^3: 136 (8), 95 (4)*, 127 (2).
 inline int slab_planes(const BlockSet *sets, size_t n_sets, bool f64, int n_cu) {
   int largest = 0, smallest = 64;
   for (size_t i = 0; i < n_sets; i++) {
